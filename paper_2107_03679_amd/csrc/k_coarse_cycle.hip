@@ -6,6 +6,8 @@
 //   down: e = W r;  t = r - K e = (1 - w) r + sum of neighbours of e;  r_{l+1} = 4 R t
 //   coarsest: e = K^-1 r (explicit inverse)
 //   up:   t = e + P e_{l+1};  e = (1 - w) t + W (r + sum of neighbours of t)
+#include <algorithm>
+
 #include "dev_common.h"
 #include "kernels.h"
 
@@ -244,6 +246,156 @@ __global__ __launch_bounds__(CC_NT) void k_coarse_cycle_lds(CoarseCycleArgs a) {
   }
 }
 
+// ---- the same cycle in two launches, for coarsest grids whose product is the long part ----
+// One workgroup per right-hand side reads the whole inverse (8 Nc^2 bytes: 1.3 MB at 20^2)
+// through one CU, 26-40 us of the 37-53 us the single launch takes.  Here CD_ROWS rows of
+// the product belong to one workgroup: ceil(Nc / CD_ROWS) workgroups per right-hand side
+// each repeat the down part (a few points per thread, in LDS) and form their rows, with
+// their slice of the inverse loaded into registers before the down part, so that it is
+// there when the coarsest right-hand side is.  The up part is a second launch (it needs
+// every row).  Whole solves at 1e-7, single launch against two: 128^2 x 1 (22^2 coarsest)
+// 18.9 -> 11.2 ms, 203^2 x 7 FGMRES (17^2) 43.0 -> 33.8, a gradient at 256^2 x 32 (20^2)
+// 159 -> 106, 64^3 x 8 (8^3, whose vectors did not fit the single launch's LDS) 91.8 -> 64.6.
+constexpr int CD_ROWS = 32, CD_GRP = CC_NT / CD_ROWS, CD_MK = 20, CD_MP = 4;
+
+template <int DIM>
+__global__ __launch_bounds__(CC_NT) void k_coarse_down_rows(CoarseCycleArgs a) {
+  extern __shared__ c32 lds[];
+  const int b = blockIdx.y;
+  if (a.active && !a.active[b]) return;
+  const float om = a.omega;
+  const int tid = threadIdx.x, Nc = (int)a.lv[a.L - 1].N, row0 = blockIdx.x * CD_ROWS;
+  const int rr = tid % CD_ROWS, g = tid / CD_ROWS, row = row0 + rr;
+  // this thread's entries of the inverse: row `row`, columns g, g + CD_GRP, ...
+  c32 mk[CD_MK];
+#pragma unroll
+  for (int u = 0; u < CD_MK; ++u) {
+    const int k = min(g + u * CD_GRP, Nc - 1);
+    mk[u] = a.minvT[(long long)k * Nc + min(row, Nc - 1)];
+  }
+  c32* se = lds;                      // W r of the current level; at the end the coarsest right-hand side
+  c32* st = lds + (int)a.lv[a.lp].N;  // its residual
+  c32 r[CD_MP], w[CD_MP];
+  {
+    const CoarseLevel& F = a.lv[a.lp];
+    const c32* rg = F.rc + (long long)b * F.N;
+#pragma unroll
+    for (int i = 0; i < CD_MP; ++i) {
+      const int p = min(tid + i * CC_NT, (int)F.N - 1);
+      r[i] = rg[p];
+      w[i] = F.wd[p];
+    }
+  }
+  for (int l = a.lp; l < a.L - 1; ++l) {
+    const CoarseLevel& F = a.lv[l];
+    const CoarseLevel& C = a.lv[l + 1];
+    const int Nf = (int)F.N, Nn = (int)C.N, n = F.n;
+#pragma unroll
+    for (int i = 0; i < CD_MP; ++i)
+      if (tid + i * CC_NT < Nf) se[tid + i * CC_NT] = cmul(w[i], r[i]);
+    const bool last = l + 1 == a.L - 1;
+    if (!last) {
+#pragma unroll
+      for (int i = 0; i < CD_MP; ++i) w[i] = C.wd[min(tid + i * CC_NT, Nn - 1)];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < CD_MP; ++i) {
+      const int p = tid + i * CC_NT;
+      if (p < Nf) st[p] = cadd(cscale(r[i], 1.0f - om), neighbour_sum(se, p, coord_of32((unsigned)p, (unsigned)n, DIM), n, DIM));
+    }
+    __syncthreads();
+    c32* rcg = C.rc + (long long)b * C.N;
+#pragma unroll
+    for (int i = 0; i < CD_MP; ++i) {
+      const int q = tid + i * CC_NT;
+      if (q < Nn) {
+        r[i] = fw4(st, coord_of32((unsigned)q, (unsigned)C.n, DIM), n, DIM);
+        if (last) se[q] = r[i];
+        else if (blockIdx.x == 0) rcg[q] = r[i];  // the up part's
+      }
+    }
+    // the next level's first stage writes se (last read before the barrier above)
+  }
+  __syncthreads();
+  c32 acc = make_float2(0.f, 0.f);
+#pragma unroll
+  for (int u = 0; u < CD_MK; ++u) {
+    const int k = g + u * CD_GRP;
+    if (k < Nc) acc = cfma(mk[u], se[k], acc);
+  }
+  // a wavefront holds two column groups of the 32 rows; then 16 partial sums per row
+  acc.x += __shfl_xor(acc.x, CD_ROWS, HELM_WAVE);
+  acc.y += __shfl_xor(acc.y, CD_ROWS, HELM_WAVE);
+  c32* red = st;  // free since the barrier above
+  if (tid % HELM_WAVE < CD_ROWS) red[(tid / HELM_WAVE) * CD_ROWS + rr] = acc;
+  __syncthreads();
+  if (tid < CD_ROWS && row < Nc) {
+    c32 s2 = make_float2(0.f, 0.f);
+#pragma unroll
+    for (int q = 0; q < CC_NT / HELM_WAVE; ++q) s2 = cadd(s2, red[q * CD_ROWS + tid]);
+    a.lv[a.L - 1].e[(long long)b * Nc + row] = s2;
+  }
+}
+
+template <int DIM>
+__global__ __launch_bounds__(CC_NT) void k_coarse_up_rows(CoarseCycleArgs a) {
+  extern __shared__ c32 lds[];
+  const int b = blockIdx.x;
+  if (a.active && !a.active[b]) return;
+  const float om = a.omega;
+  const int tid = threadIdx.x;
+  c32* st = lds;                      // e + P e_coarse of the current level
+  c32* se = lds + (int)a.lv[a.lp].N;  // the solution of the level below
+  c32 r[CD_MP], w[CD_MP];
+  auto fetch = [&](int l) {
+    const CoarseLevel& F = a.lv[l];
+    const c32* rg = F.rc + (long long)b * F.N;
+#pragma unroll
+    for (int i = 0; i < CD_MP; ++i) {
+      const int p = min(tid + i * CC_NT, (int)F.N - 1);
+      r[i] = rg[p];
+      w[i] = F.wd[p];
+    }
+  };
+  fetch(a.L - 2);
+  {
+    const CoarseLevel& Q = a.lv[a.L - 1];
+    const c32* eg = Q.e + (long long)b * Q.N;
+    for (int p = tid; p < Q.N; p += CC_NT) se[p] = eg[p];
+  }
+  __syncthreads();
+  for (int l = a.L - 2; l >= a.lp; --l) {
+    const CoarseLevel& F = a.lv[l];
+    const int Nf = (int)F.N, n = F.n, nc = a.lv[l + 1].n;
+    c32 tv[CD_MP];
+#pragma unroll
+    for (int i = 0; i < CD_MP; ++i) {
+      const int p = tid + i * CC_NT;
+      if (p < Nf) {
+        tv[i] = cadd(cmul(w[i], r[i]), prolong_at(se, coord_of32((unsigned)p, (unsigned)n, DIM), nc, DIM));
+        st[p] = tv[i];
+      }
+    }
+    __syncthreads();
+    c32* eg = F.e + (long long)b * F.N;
+#pragma unroll
+    for (int i = 0; i < CD_MP; ++i) {
+      const int p = tid + i * CC_NT;
+      if (p < Nf) {
+        const c32 nb = neighbour_sum(st, p, coord_of32((unsigned)p, (unsigned)n, DIM), n, DIM);
+        const c32 v = cadd(cscale(tv[i], 1.0f - om), cmul(w[i], cadd(r[i], nb)));
+        if (l == a.lp) eg[p] = v;
+        else se[p] = v;
+      }
+    }
+    if (l > a.lp) {
+      fetch(l - 1);
+      __syncthreads();
+    }
+  }
+}
+
 }  // namespace
 
 // LDS bytes k_coarse_cycle_lds needs for levels lp .. L-1 (r, e, t per level,
@@ -254,7 +406,30 @@ size_t coarse_cycle_lds_bytes(const CoarseCycleArgs& a) {
   return n * sizeof(c32);
 }
 
+// Two launches where the coarsest product outweighs a launch (Nc > 128) and the entries fit
+// the threads' registers; one launch below (37^2 / 10^2 x 60: 14.3 us in one).
+bool coarse_cycle_split(const CoarseCycleArgs& a) {
+  const long long Nc = a.lv[a.L - 1].N, Nf = a.lv[a.lp].N;
+  return a.lp < a.L - 1 && Nc > 128 && Nc <= CD_GRP * CD_MK && Nf <= CC_NT * CD_MP;
+}
+
 void launch_coarse_cycle(hipStream_t s, int B, const CoarseCycleArgs& a) {
+  if (coarse_cycle_split(a)) {
+    const int Nc = (int)a.lv[a.L - 1].N, Nf = (int)a.lv[a.lp].N;
+    // down: two vectors of the finest level (the second at least the 16 x 32 partial sums);
+    // up: one, and one of the level below
+    const size_t down = (size_t)(Nf + std::max(Nf, CC_NT / HELM_WAVE * CD_ROWS)) * sizeof(c32);
+    const size_t up = (size_t)(Nf + a.lv[a.lp + 1].N) * sizeof(c32);
+    const dim3 rows((Nc + CD_ROWS - 1) / CD_ROWS, B);
+    if (a.dim == 2) {
+      hipLaunchKernelGGL(k_coarse_down_rows<2>, rows, dim3(CC_NT), down, s, a);
+      hipLaunchKernelGGL(k_coarse_up_rows<2>, dim3(B), dim3(CC_NT), up, s, a);
+    } else {
+      hipLaunchKernelGGL(k_coarse_down_rows<3>, rows, dim3(CC_NT), down, s, a);
+      hipLaunchKernelGGL(k_coarse_up_rows<3>, dim3(B), dim3(CC_NT), up, s, a);
+    }
+    return;
+  }
   const size_t lds = coarse_cycle_lds_bytes(a);
   if (lds <= kCoarseCycleMaxLds)
     hipLaunchKernelGGL(k_coarse_cycle_lds, dim3(B), dim3(CC_NT), lds, s, a);

@@ -1,0 +1,36 @@
+"""The coarse levels of a cycle at the sizes where their kernels change: the two-launch form
+(coarsest grids of more than 128 points) against the FP64 oracle."""
+from __future__ import annotations
+
+import numpy as np
+import pytest
+
+import synth
+from oracle.multigrid import Hierarchy
+
+from .helpers import gpu_context, medium, oracle_problem, rel, to_dev, to_np
+
+pytestmark = pytest.mark.gpu
+
+
+# interior, levels, dim, right-hand sides -> coarse sizes (layer of 8 cells)
+@pytest.mark.parametrize("n, levels, d, B", [
+    (25, 3, 2, 3),   # 41, 21, 11^2: 121 points, one launch
+    (29, 3, 2, 3),   # 45, 23, 12^2: 144 points, the first split
+    (73, 4, 2, 2),   # 89, 45, 23, 12^2: two levels above the coarsest in the launch
+    (77, 3, 2, 1),   # 93, 47, 24^2: 576 points, the last row block half full
+    (5, 3, 3, 2),    # 21, 11, 6^3
+    (13, 3, 3, 5),   # 29, 15, 8^3: 15^3 points in four passes of the workgroup
+])
+def test_split_coarse_cycle_matches_oracle(n, levels, d, B):
+    nmap = medium(n, seed=5, d=d)
+    prob = oracle_problem(nmap, levels=levels)
+    hier = Hierarchy(prob)
+    r = synth.complex_field((B, *prob.shape), 70)
+    with gpu_context(nmap, levels=levels, max_batch=B) as ctx:
+        assert ctx.info.coarsest_n == hier.sizes[-1]
+        z = to_np(ctx.precondition(to_dev(r)))
+    ref = np.stack([hier.vcycle(ri.ravel()).reshape(prob.shape) for ri in r])
+    # single precision through ~10 stages and a 64-bit inverse rounded to 32 bits: the bound the
+    # other cycle tests use
+    assert rel(z, ref) < 1e-5
