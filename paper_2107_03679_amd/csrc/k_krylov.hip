@@ -942,16 +942,16 @@ namespace {
 // of the plane and a one-point ring.  Each plane of Z_j is read once per
 // column (the flat kernel's z-neighbours, a plane apart, mostly miss the L2).
 constexpr int MX = 64, MY = 8, MZ = 16, MT = 256;
-__global__ __launch_bounds__(MT) void k_matvec_march3(int nrhs, KrylovArgs k, int j, LevelArgs fine) {
+__global__ __launch_bounds__(MT) void k_matvec_march3(int nrhs, KrylovArgs k, int j, LevelArgs fine, int planes) {
   __shared__ c32 sP[MY + 2][MX + 2];
   const int n = fine.n;
   const int tx_n = (n + MX - 1) / MX, ty_n = (n + MY - 1) / MY;
-  const unsigned tiles = (unsigned)(tx_n * ty_n * ((n + MZ - 1) / MZ));
+  const unsigned tiles = (unsigned)(tx_n * ty_n * ((n + planes - 1) / planes));
   const TileId id = xcd_tile(blockIdx.x, nrhs, tiles, HELM_RHS_GROUP);
   const int b = id.b;
   if (!k.active[b]) return;
-  const int x0 = (id.t % tx_n) * MX, y0 = ((id.t / tx_n) % ty_n) * MY, z0 = (id.t / (tx_n * ty_n)) * MZ;
-  const int z1 = min(n, z0 + MZ);
+  const int x0 = (id.t % tx_n) * MX, y0 = ((id.t / tx_n) % ty_n) * MY, z0 = (id.t / (tx_n * ty_n)) * planes;
+  const int z1 = min(n, z0 + planes);
   const c32* zv = k.Z + zidx(k, b, j);
   c32* wv = k.V + vidx(k, b, j + 1);
   const long long n2 = (long long)n * n;
@@ -1161,8 +1161,10 @@ __global__ __launch_bounds__(MT) void k_residual_ff_march3(int nrhs, KrylovArgs 
 void launch_sstep_matvec(hipStream_t s, int B, const KrylovArgs& k, int j, const LevelArgs& fine) {
   if (k.dim == 3) {
     const int n = fine.n;
-    const int tiles = ((n + MX - 1) / MX) * ((n + MY - 1) / MY) * ((n + MZ - 1) / MZ);
-    hipLaunchKernelGGL(k_matvec_march3, dim3(B * tiles), dim3(MT), 0, s, B, k, j, fine);
+    const int cols = ((n + MX - 1) / MX) * ((n + MY - 1) / MY);
+    const int planes = march_planes((long long)B * cols, n, MZ, 2);
+    hipLaunchKernelGGL(k_matvec_march3, dim3(B * cols * ((n + planes - 1) / planes)), dim3(MT), 0, s, B, k, j, fine,
+                       planes);
     return;
   }
   hipLaunchKernelGGL(k_sstep_matvec, dim3(B * k.nblk), dim3(NT), 0, s, B, k, j, fine);

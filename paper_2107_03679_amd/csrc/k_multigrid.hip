@@ -774,19 +774,19 @@ __global__ __launch_bounds__(256) void k_step_col(int nrhs, VecSet r, ScaleSet r
 // full weighting is added to the coarse plane(s) it belongs to (weight 1/2 for
 // f - 1 = 2K, 1/4 to K - 1 and K for f - 1 = 2K - 1), accumulated in
 // registers; a coarse plane is written once complete.
-constexpr int DCX = 30, DCY = 8, DKZ = 8, DRX = 2 * DCX + 3, DRY = 2 * DCY + 3, DIV = (DRY + 3) / 4;
+constexpr int DCX = 30, DCY = 8, DRX = 2 * DCX + 3, DRY = 2 * DCY + 3, DIV = (DRY + 3) / 4;
 __global__ __launch_bounds__(256) void k_down_march3c(int nrhs, VecSet r, ScaleSet rs, LevelArgs lv, float omega,
-                                                      VecSet rc, int nc, const int* active) {
+                                                      VecSet rc, int nc, const int* active, int planes) {
   __shared__ c32 sV[2][4 * DIV][64];
   __shared__ c32 sS[4 * DIV][64];
   const int n = lv.n;
   const int tx_n = (nc + DCX - 1) / DCX, ty_n = (nc + DCY - 1) / DCY;
-  const unsigned tiles = (unsigned)(tx_n * ty_n * ((nc + DKZ - 1) / DKZ));
+  const unsigned tiles = (unsigned)(tx_n * ty_n * ((nc + planes - 1) / planes));
   const TileId id = xcd_tile(blockIdx.x, nrhs, tiles, HELM_RHS_GROUP);
   const int b = id.b;
   if (active && !active[b]) return;
-  const int cx0 = (id.t % tx_n) * DCX, cy0 = ((id.t / tx_n) % ty_n) * DCY, kz0 = (id.t / (tx_n * ty_n)) * DKZ;
-  const int kz1 = min(nc, kz0 + DKZ);
+  const int cx0 = (id.t % tx_n) * DCX, cy0 = ((id.t / tx_n) % ty_n) * DCY, kz0 = (id.t / (tx_n * ty_n)) * planes;
+  const int kz1 = min(nc, kz0 + planes);
   const int fx0 = 2 * cx0 - 2, fy0 = 2 * cy0 - 2;
   const float sc = scale_of(rs, b);
   const c32* rb = r.p + (long long)b * r.stride;
@@ -884,20 +884,21 @@ __global__ __launch_bounds__(256) void k_down_march3c(int nrhs, VecSet r, ScaleS
 // reads are kept two at a time in LDS), then z(f - 1) from v2(f - 2 .. f).  With acc
 // the leg adds z to the output instead of overwriting it (a repeated coarse visit:
 // e + MG(r - K e, 0) without a separate pass).
-constexpr int UX = 64, UY = 8, UZ = 16, URING = 2 * (UX + 2) + 2 * UY;
+constexpr int UX = 64, UY = 8, URING = 2 * (UX + 2) + 2 * UY;
 __global__ __launch_bounds__(256) void k_up_march3c(int nrhs, VecSet r, ScaleSet rs, LevelArgs lv, float omega,
-                                                    VecSet ec, int nc, VecSet z, const int* active, int acc) {
+                                                    VecSet ec, int nc, VecSet z, const int* active, int acc,
+                                                    int planes) {
   constexpr int CX = UX / 2 + 2, CY = UY / 2 + 2, NCP = CX * CY, ITC = (NCP + 255) / 256;
   __shared__ c32 sE[2][CY][CX];
   __shared__ c32 sV[2][UY + 2][UX + 2];
   const int n = lv.n;
   const int tx_n = (n + UX - 1) / UX, ty_n = (n + UY - 1) / UY;
-  const unsigned tiles = (unsigned)(tx_n * ty_n * ((n + UZ - 1) / UZ));
+  const unsigned tiles = (unsigned)(tx_n * ty_n * ((n + planes - 1) / planes));
   const TileId id = xcd_tile(blockIdx.x, nrhs, tiles, HELM_RHS_GROUP);
   const int b = id.b;
   if (active && !active[b]) return;
-  const int fx0 = (id.t % tx_n) * UX, fy0 = ((id.t / tx_n) % ty_n) * UY, fz0 = (id.t / (tx_n * ty_n)) * UZ;
-  const int fz1 = min(n, fz0 + UZ);
+  const int fx0 = (id.t % tx_n) * UX, fy0 = ((id.t / tx_n) % ty_n) * UY, fz0 = (id.t / (tx_n * ty_n)) * planes;
+  const int fz1 = min(n, fz0 + planes);
   const int cxs = fx0 / 2 - 1, cys = fy0 / 2 - 1;
   const float sc = scale_of(rs, b);
   const c32* rb = r.p + (long long)b * r.stride;
@@ -1129,18 +1130,18 @@ __global__ void k_level_residual(int dim, VecSet bvec, ScaleSet bs, VecSet v, Le
 // one-point ring, the planes below and above in registers with the next plane's
 // loads in flight (the flat kernel's z-neighbours, a plane apart, mostly miss the
 // L2).  Neighbours summed in the order of neighbour_sum (zero outside the grid).
-constexpr int RMX = 64, RMY = 8, RMZ = 16;
+constexpr int RMX = 64, RMY = 8;
 __global__ __launch_bounds__(256) void k_level_residual_march3(int nrhs, VecSet bvec, ScaleSet bs, VecSet v,
-                                                               LevelArgs lv, VecSet out, const int* active) {
+                                                               LevelArgs lv, VecSet out, const int* active, int planes) {
   __shared__ c32 sP[RMY + 2][RMX + 2];
   const int n = lv.n;
   const int tx_n = (n + RMX - 1) / RMX, ty_n = (n + RMY - 1) / RMY;
-  const unsigned tiles = (unsigned)(tx_n * ty_n * ((n + RMZ - 1) / RMZ));
+  const unsigned tiles = (unsigned)(tx_n * ty_n * ((n + planes - 1) / planes));
   const TileId id = xcd_tile(blockIdx.x, nrhs, tiles, HELM_RHS_GROUP);
   const int b = id.b;
   if (active && !active[b]) return;
-  const int x0 = (id.t % tx_n) * RMX, y0 = ((id.t / tx_n) % ty_n) * RMY, z0 = (id.t / (tx_n * ty_n)) * RMZ;
-  const int z1 = min(n, z0 + RMZ);
+  const int x0 = (id.t % tx_n) * RMX, y0 = ((id.t / tx_n) % ty_n) * RMY, z0 = (id.t / (tx_n * ty_n)) * planes;
+  const int z1 = min(n, z0 + planes);
   const c32* vb = v.p + (long long)b * v.stride;
   const c32* bb = bvec.p + (long long)b * bvec.stride;
   c32* ob = out.p + (long long)b * out.stride;
@@ -1375,15 +1376,19 @@ void up_tile(hipStream_t s, int B, VecSet r, ScaleSet rs, LevelArgs lv, float om
 
 void launch_down_fused3(hipStream_t s, int B, VecSet r, ScaleSet rs, LevelArgs lv, float omega, VecSet rc, int nc,
                         const int* active) {
-  const int tiles = ((nc + DCX - 1) / DCX) * ((nc + DCY - 1) / DCY) * ((nc + DKZ - 1) / DKZ);
-  hipLaunchKernelGGL(k_down_march3c, dim3(B * tiles), dim3(256), 0, s, B, r, rs, lv, omega, rc, nc, active);
+  const int cols = ((nc + DCX - 1) / DCX) * ((nc + DCY - 1) / DCY);
+  const int planes = march_planes((long long)B * cols, nc, 8, 1);
+  hipLaunchKernelGGL(k_down_march3c, dim3(B * cols * ((nc + planes - 1) / planes)), dim3(256), 0, s, B, r, rs, lv,
+                     omega, rc, nc, active, planes);
 }
 
 void launch_up_fused3(hipStream_t s, int B, VecSet r, ScaleSet rs, LevelArgs lv, float omega, VecSet ec, int nc,
                       VecSet z, const int* active, int acc) {
   const int n = lv.n;
-  const int tiles = ((n + UX - 1) / UX) * ((n + UY - 1) / UY) * ((n + UZ - 1) / UZ);
-  hipLaunchKernelGGL(k_up_march3c, dim3(B * tiles), dim3(256), 0, s, B, r, rs, lv, omega, ec, nc, z, active, acc);
+  const int cols = ((n + UX - 1) / UX) * ((n + UY - 1) / UY);
+  const int planes = march_planes((long long)B * cols, n, 16, 2);
+  hipLaunchKernelGGL(k_up_march3c, dim3(B * cols * ((n + planes - 1) / planes)), dim3(256), 0, s, B, r, rs, lv, omega,
+                     ec, nc, z, active, acc, planes);
 }
 
 template <int TY, int K>
@@ -1541,8 +1546,10 @@ void launch_level_residual(hipStream_t s, int dim, int B, VecSet bvec, VecSet v,
                            const int* active, ScaleSet bs) {
   if (dim == 3) {
     const int n = lv.n;
-    const int tiles = ((n + RMX - 1) / RMX) * ((n + RMY - 1) / RMY) * ((n + RMZ - 1) / RMZ);
-    hipLaunchKernelGGL(k_level_residual_march3, dim3(B * tiles), dim3(256), 0, s, B, bvec, bs, v, lv, out, active);
+    const int cols = ((n + RMX - 1) / RMX) * ((n + RMY - 1) / RMY);
+    const int planes = march_planes((long long)B * cols, n, 16, 2);
+    hipLaunchKernelGGL(k_level_residual_march3, dim3(B * cols * ((n + planes - 1) / planes)), dim3(256), 0, s, B, bvec,
+                       bs, v, lv, out, active, planes);
     return;
   }
   hipLaunchKernelGGL(k_level_residual, dim3(nblocks(lv.N, 256), B), dim3(256), 0, s, dim, bvec, bs, v, lv, out,

@@ -1,5 +1,6 @@
-"""The coarse levels of a cycle at the sizes where their kernels change: the two-launch form
-(coarsest grids of more than 128 points) against the FP64 oracle."""
+"""The levels of a cycle at the sizes where their kernels or launches change: the two-launch
+form of the coarse levels (coarsest grids of more than 128 points) against the FP64 oracle,
+the march lengths of the 3D legs against each other."""
 from __future__ import annotations
 
 import numpy as np
@@ -34,3 +35,16 @@ def test_split_coarse_cycle_matches_oracle(n, levels, d, B):
     # single precision through ~10 stages and a 64-bit inverse rounded to 32 bits: the bound the
     # other cycle tests use
     assert rel(z, ref) < 1e-5
+
+
+@pytest.mark.parametrize("n, B", [(31, 48), (18, 200)])
+def test_march_lengths_agree(n, B):
+    """A batch marches through more planes per workgroup than one right-hand side (49^3: 16 and 2
+    planes in the finest up-leg); every point is the same arithmetic, so the fields are equal
+    (four levels: with three the coarsest grid is solved alone, by another kernel at B < 4)."""
+    nmap = medium(n, seed=6, d=3)
+    with gpu_context(nmap, levels=4, max_batch=B, restart=4, cycle=3) as ctx:
+        r = to_dev(synth.complex_field((1, *ctx.grid_shape()), 71))
+        one = ctx.precondition(r)
+        many = ctx.precondition(r.expand(B, *ctx.grid_shape()).contiguous())
+        assert bool((many == one).all())
