@@ -93,12 +93,9 @@ struct helm_ctx {
   float* d_tv_mag = nullptr;   // [n^dim] TV magnitudes
   float* d_tv_part = nullptr;  // per-block TV partial sums
   double2* d_gram = nullptr;   // [maxB][nblk][(m+1)(m+2)/2] Gram partials of the s-step form
-  // inverse-problem workspace (allocated on first use): FGP dual p and its
-  // extrapolation r [dim][n^dim], primal w, prox input v, index map from f
-  float* d_inv_p = nullptr;
-  float* d_inv_r = nullptr;
-  float* d_inv_w = nullptr;
-  float* d_inv_v = nullptr;
+  // inverse-problem workspace (allocated on first use): the FGP prox's buffers, index map
+  // from f
+  FgpBufs inv{};
   float* d_inv_n = nullptr;
   double* d_inv_part = nullptr;
   int inv_part_len = 0;
@@ -1609,13 +1606,14 @@ int helm_tv(helm_ctx* c, const float* n_map, double eps, double scale, float* gr
 // ---------------------------------------------------------------- inverse problem (Sec. V, Alg. 4)
 namespace {
 void inv_reserve(helm_ctx* c) {
-  if (c->d_inv_p) return;
-  const long long Ni = npts(c->n, c->dim);
-  c->d_inv_p = c->alloc<float>((size_t)c->dim * Ni);
-  c->d_inv_r = c->alloc<float>((size_t)c->dim * Ni);
-  c->d_inv_w = c->alloc<float>(Ni);
-  c->d_inv_v = c->alloc<float>(Ni);
-  c->d_inv_n = c->alloc<float>(Ni);
+  if (!c->d_inv_n) c->d_inv_n = c->alloc<float>(npts(c->n, c->dim));
+}
+// the prox's buffers, one allocation
+void prox_reserve(helm_ctx* c) {
+  if (c->inv.p[0]) return;
+  const size_t Ni = (size_t)npts(c->n, c->dim), Nd = c->dim * Ni;
+  float* m = c->alloc<float>(4 * Nd + 2 * Ni);
+  c->inv = FgpBufs{{m, m + Nd}, {m + 2 * Nd, m + 3 * Nd}, m + 4 * Nd, m + 4 * Nd + Ni};
 }
 }  // namespace
 
@@ -1737,10 +1735,13 @@ int helm_tv_prox(helm_ctx* c, const float* v_dev, double lam, double lo, int ite
   if (!c || !v_dev || !w_dev) return fail(c, HELM_EINVAL, "null argument");
   if (iters < 0 || !(lam >= 0.0) || !std::isfinite(lam)) return fail(c, HELM_EINVAL, "bad lam or iters");
   HELM_GUARD_BEGIN
-  inv_reserve(c);
-  launch_tv_prox(c->s, c->dim, c->n, v_dev, (float)lam, (float)lo, iters, c->d_inv_p, c->d_inv_r, c->d_inv_w);
-  check(hipMemcpyAsync(w_dev, c->d_inv_w, (size_t)npts(c->n, c->dim) * sizeof(float), hipMemcpyDeviceToDevice, c->s),
-        "copy w");
+  prox_reserve(c);
+  // the last launch reads v around each point it writes: an overlapping w is written last
+  const size_t Ni = (size_t)npts(c->n, c->dim);
+  const bool over = w_dev < v_dev + Ni && v_dev < w_dev + Ni;
+  launch_tv_prox(c->s, c->dim, c->n, v_dev, (float)lam, (float)lo, iters, c->inv, over ? c->inv.w : w_dev);
+  if (over)
+    check(hipMemcpyAsync(w_dev, c->inv.w, Ni * sizeof(float), hipMemcpyDeviceToDevice, c->s), "copy w");
   HELM_GUARD_END("tv_prox")
 }
 
@@ -1750,13 +1751,10 @@ int helm_fbs_step(helm_ctx* c, float* f_dev, float* fbar_dev, const float* grad_
   if (!(gamma > 0.0) || !(tau >= 0.0) || prox_iters < 0 || !(*alpha_host >= 1.0))
     return fail(c, HELM_EINVAL, "bad gamma, tau, prox_iters or alpha");
   HELM_GUARD_BEGIN
-  inv_reserve(c);
-  const long long Ni = npts(c->n, c->dim);
-  launch_axmy(c->s, Ni, fbar_dev, (float)gamma, grad_dev, c->d_inv_v);
-  launch_tv_prox(c->s, c->dim, c->n, c->d_inv_v, (float)(gamma * tau), (float)lo, prox_iters, c->d_inv_p, c->d_inv_r,
-                 c->d_inv_w);
+  prox_reserve(c);
   const double a = *alpha_host, an = 0.5 * (1.0 + std::sqrt(1.0 + 4.0 * a * a));
-  launch_fbs_momentum(c->s, Ni, c->d_inv_w, (float)((a - 1.0) / an), f_dev, fbar_dev);
+  const FbsArgs fm{f_dev, fbar_dev, grad_dev, (float)gamma, (float)((a - 1.0) / an)};
+  launch_tv_prox(c->s, c->dim, c->n, nullptr, (float)(gamma * tau), (float)lo, prox_iters, c->inv, nullptr, &fm);
   *alpha_host = an;
   HELM_GUARD_END("fbs_step")
 }

@@ -216,10 +216,21 @@ void launch_sstep_matvec(hipStream_t s, int B, const KrylovArgs& k, int j, const
 void launch_sstep_gram_solve(hipStream_t s, int B, const KrylovArgs& k, const LevelArgs& fine, double2* part);
 
 // ---- inverse problem (Sec. V, Alg. 4), interior grid n^dim ----
-void launch_tv_prox(hipStream_t s, int dim, int n, const float* v, float lam, float lo, int iters, float* p, float* r,
-                    float* w);
-void launch_axmy(hipStream_t s, long long count, const float* a, float sc, const float* b, float* out);
-void launch_fbs_momentum(hipStream_t s, long long count, const float* f_new, float beta, float* f, float* fbar);
+// work buffers: dual field and its extrapolation [dim][n^dim], two of each (the steps of one
+// launch read one and write the other), prox input and result [n^dim]
+struct FgpBufs {
+  float *p[2], *r[2], *v, *w;
+};
+// the update of Alg. 4 around the prox: v = fbar - gamma grad, then with the prox's result w
+// fbar = w + beta (w - f), f = w
+struct FbsArgs {
+  float *f, *fbar;
+  const float* grad;
+  float gamma, beta;
+};
+// w = prox(v), or with fm the update of fm->f and fm->fbar (v and w unused)
+void launch_tv_prox(hipStream_t s, int dim, int n, const float* v, float lam, float lo, int iters, const FgpBufs& bufs,
+                    float* w, const FbsArgs* fm = nullptr);
 // ---- medium-dependent set-up (k_setup.hip) ----
 struct SetupFineArgs {
   int dim, n, w, ne;
