@@ -76,6 +76,8 @@ struct helm_ctx {
   std::vector<Level> lv;
   c32* d_minvT = nullptr;
   c32* d_cs_part = nullptr;  // slice partials of the coarsest solve as a matrix product
+  double2* d_inv_work = nullptr;  // the coarsest operator being inverted (complex double)
+  int* d_inv_flag = nullptr;      // set where it needs pivoting
   int Nc = 0;
 
   // Krylov workspace
@@ -818,7 +820,8 @@ std::pair<float, float> split_ff(double v) {
 
 // Per medium: the Omega values of the fine planes and the coarse interiors on the GPU
 // (k_setup.hip), then the exact inverse of the coarsest shifted operator from that level's
-// coefficients (host FP64, a few hundred to a few thousand unknowns), uploaded.
+// coefficients (FP64, a few hundred to a few thousand unknowns; k_coarse_inverse.hip, on the host
+// where it needs pivoting).
 void update_medium(helm_ctx* c, const float* n_map_dev) {
   const long long Ni = npts(c->n, c->dim);
   check(hipMemcpyAsync(c->d_nmap, n_map_dev, Ni * sizeof(float), hipMemcpyDeviceToDevice, c->s), "copy n_map");
@@ -848,6 +851,14 @@ void update_medium(helm_ctx* c, const float* n_map_dev) {
                         (float)c->o.omega_jac, c->lv[l].kc, c->lv[l].kclo, c->lv[l].wd);
   check(hipGetLastError(), "set-up kernels");
   const Level& cl = c->lv[c->L - 1];
+  check(hipMemcpyAsync(c->d_inv_flag, c->d_zero_ints, sizeof(int), hipMemcpyDeviceToDevice, c->s), "reset");
+  launch_coarse_inverse(c->s, c->dim, cl.n, cl.kc, cl.kclo, c->kbh * std::ldexp(1.0, c->L - 1), c->d_inv_work,
+                        c->d_minvT, c->d_inv_flag);
+  check(hipGetLastError(), "coarsest inverse");
+  check(hipMemcpyAsync(c->h_status, c->d_inv_flag, sizeof(int), hipMemcpyDeviceToHost, c->s), "inverse flag");
+  check(hipStreamSynchronize(c->s), "set-up");
+  if (c->h_status[0] == 0) return;
+  // rows that are not diagonally dominant (or not finite): pivoted elimination on the host
   std::vector<c32> kc32(cl.N), kclo32(cl.N);
   check(hipMemcpyAsync(kc32.data(), cl.kc, cl.N * sizeof(c32), hipMemcpyDeviceToHost, c->s), "coarsest kc");
   check(hipMemcpyAsync(kclo32.data(), cl.kclo, cl.N * sizeof(c32), hipMemcpyDeviceToHost, c->s), "coarsest kc");
@@ -1106,6 +1117,8 @@ int helm_setup(const helm_grid* grid, const float* n_map_dev, double k0, const h
     c->Nc = (int)c->lv[c->L - 1].N;
     c->d_minvT = c->alloc<c32>((size_t)c->Nc * c->Nc);
     c->d_cs_part = c->alloc<c32>(coarse_solve_part_size(maxB, c->Nc));
+    c->d_inv_work = c->alloc<double2>(coarse_inverse_work(c->Nc));
+    c->d_inv_flag = c->alloc<int>(1);
     c->d_nmap = c->alloc<float>(npts(c->n, c->dim));
     c->d_f = c->alloc<float>(N0);
     c->d_chi = c->alloc<c32>(N0);
@@ -1216,19 +1229,10 @@ int helm_plane_wave_rhs(helm_ctx* c, int B, const double* dirs, helm_c32* rhs, h
   if (!c || !dirs || !rhs) return fail(c, HELM_EINVAL, "null argument");
   if (B < 1 || B > c->o.max_batch) return fail(c, HELM_EINVAL, "B must be in [1, max_batch]");
   const int ne = c->ne, dim = c->dim;
-  std::vector<c32> tab((size_t)B * dim * ne);
   const double centre = c->w + 0.5 * (c->n - 1);
-  for (int b = 0; b < B; ++b)
-    for (int a = 0; a < dim; ++a) {
-      const double d = dirs[b * dim + a];
-      for (int i = 0; i < ne; ++i) {
-        const double ph = c->kbh * d * (i - centre);
-        tab[((size_t)b * dim + a) * ne + i] = make_float2((float)std::cos(ph), (float)std::sin(ph));
-      }
-    }
   try {
     check(hipStreamSynchronize(c->user_s), "caller stream");
-    check(hipMemcpyAsync(c->d_tables, tab.data(), tab.size() * sizeof(c32), hipMemcpyHostToDevice, c->s), "tables");
+    launch_plane_tables(c->s, dim, B, ne, c->kbh, centre, dirs, c->d_tables);
     launch_plane_wave(c->s, dim, B, ne, c->d_f, c->d_tables, (c32*)rhs, (c32*)u_in);
     check(hipGetLastError(), "plane wave");
     check(hipStreamSynchronize(c->s), "sync");
@@ -1624,7 +1628,6 @@ int helm_update_f(helm_ctx* c, const float* f_dev) {
     inv_reserve(c);
     launch_index_from_f(c->s, npts(c->n, c->dim), f_dev, 1.0 / (c->k0 * c->k0), c->o.n_b * c->o.n_b, c->d_inv_n);
     check(hipGetLastError(), "index_from_f");
-    check(hipStreamSynchronize(c->s), "sync");
     update_medium(c, c->d_inv_n);
   } catch (const HipError& e) {
     return fail(c, HELM_EHIP, std::string(e.what) + ": " + hipGetErrorString(e.code));
@@ -1642,7 +1645,6 @@ int helm_update_contrast(helm_ctx* c, const float* chi_dev) {
     // eta = sqrt(eta_b^2 + chi): the map of helm_update_f with k0^2 = 1
     launch_index_from_f(c->s, npts(c->n, c->dim), chi_dev, 1.0, c->o.n_b * c->o.n_b, c->d_inv_n);
     check(hipGetLastError(), "index_from_contrast");
-    check(hipStreamSynchronize(c->s), "sync");
     update_medium(c, c->d_inv_n);
   } catch (const HipError& e) {
     return fail(c, HELM_EHIP, std::string(e.what) + ": " + hipGetErrorString(e.code));

@@ -1,24 +1,52 @@
 // Model kernels: plane-wave right-hand sides (Sec. II-A), the refractive-index
 // gradient of Prop. 1 (Sec. V), and small elementwise helpers.
+#include <algorithm>
+
 #include "dev_common.h"
 #include "kernels.h"
 
 namespace {
 
+constexpr int PW_DIRS = 256;
+
 // rhs_q(p) = f(p) * prod_axis T_q,axis(coord_axis(p)): the plane wave
 // exp(j k_b <d_q, x - x_c>) factorises over axes; the per-axis factors are
-// tabulated on the host in FP64 and rounded once to complex64.
-__global__ void k_plane_wave(int dim, int n, long long N, const float* fplane, const c32* tables, c32* rhs,
+// tabulated in FP64 and rounded once to complex64.  (On the host the tables of
+// 60 plane waves at 577^2 were 0.6 ms of sines and cosines and an upload.)
+// Phase tables exp(j k_b h d_a (i - centre)) of up to PW_DIRS direction components (b, a):
+// tables[(b dim + a) n + i].  The phase and its sine and cosine in FP64, rounded once.
+struct PlaneDirs {
+  double d[PW_DIRS];
+};
+__global__ void k_plane_tables(int count, int n, double kbh, double centre, PlaneDirs dirs, c32* tables) {
+  const int t = blockIdx.x * blockDim.x + threadIdx.x;
+  if (t >= count * n) return;
+  const int q = t / n, i = t - q * n;
+  double sn, cs;
+  sincos(kbh * dirs.d[q] * (i - centre), &sn, &cs);
+  tables[t] = make_float2((float)cs, (float)sn);
+}
+
+// u_in = product of the axes' phases, rhs = f u_in; a point's coordinates and f serve PW_B
+// right-hand sides.
+constexpr int PW_B = 4;
+__global__ void k_plane_wave(int dim, int B, int n, long long N, const float* fplane, const c32* tables, c32* rhs,
                              c32* uin) {
-  const int b = blockIdx.y;
+  const int b0 = blockIdx.y * PW_B, b1 = min(B, b0 + PW_B);
   const long long p = (long long)blockIdx.x * blockDim.x + threadIdx.x;
   if (p >= N) return;
   const Coord c = coord_of32((unsigned)p, (unsigned)n, dim);
-  const c32* t = tables + (long long)b * dim * n;
-  c32 u = cmul(t[c.x], t[n + c.y]);
-  if (dim == 3) u = cmul(u, t[2 * n + c.z]);
-  rhs[(long long)b * N + p] = cscale(u, fplane[p]);
-  if (uin) uin[(long long)b * N + p] = u;
+  const float f = fplane[p];
+#pragma unroll
+  for (int q = 0; q < PW_B; ++q) {
+    const int b = b0 + q;
+    if (b >= b1) return;
+    const c32* t = tables + (long long)b * dim * n;
+    c32 u = cmul(t[c.x], t[n + c.y]);
+    if (dim == 3) u = cmul(u, t[2 * n + c.z]);
+    rhs[(long long)b * N + p] = cscale(u, f);
+    if (uin) uin[(long long)b * N + p] = u;
+  }
 }
 
 // grad[i] = scale * n_i * sum_q Re(conj(u_in,q + u_sc,q) (lam_q + lam2_q)) at interior point i
@@ -75,7 +103,18 @@ inline unsigned nb(long long n, int bs) { return (unsigned)((n + bs - 1) / bs); 
 void launch_plane_wave(hipStream_t s, int dim, int B, int n, const float* fplane, const c32* tables, c32* rhs,
                        c32* uin) {
   const long long N = dim == 2 ? (long long)n * n : (long long)n * n * n;
-  hipLaunchKernelGGL(k_plane_wave, dim3(nb(N, 256), B), dim3(256), 0, s, dim, n, N, fplane, tables, rhs, uin);
+  hipLaunchKernelGGL(k_plane_wave, dim3(nb(N, 256), (B + PW_B - 1) / PW_B), dim3(256), 0, s, dim, B, n, N, fplane,
+                     tables, rhs, uin);
+}
+void launch_plane_tables(hipStream_t s, int dim, int B, int n, double kbh, double centre, const double* dirs,
+                         c32* tables) {
+  for (int q = 0; q < B * dim; q += PW_DIRS) {  // the directions travel in the kernel's arguments
+    PlaneDirs d{};
+    const int count = std::min(PW_DIRS, B * dim - q);
+    std::copy(dirs + q, dirs + q + count, d.d);
+    hipLaunchKernelGGL(k_plane_tables, dim3(nb((long long)count * n, 256)), dim3(256), 0, s, count, n, kbh, centre, d,
+                       tables + (long long)q * n);
+  }
 }
 void launch_grad_n(hipStream_t s, int dim, int B, int n_e, int w, int n, const c32* uin, const c32* u,
                    const c32* lam, const float* nmap, float scale, float* grad, const c32* lam2, int accumulate) {

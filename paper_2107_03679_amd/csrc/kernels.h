@@ -181,6 +181,9 @@ void launch_accept(hipStream_t s, int B, const KrylovArgs& k, int j, const Level
 void launch_reject_reset(hipStream_t s, int B, const KrylovArgs& k, int j, const int* mg_mask, VecSet resid);
 
 // ---- model kernels ----
+// plane-wave phase tables [B][dim][n] of the directions dirs (host, [B][dim])
+void launch_plane_tables(hipStream_t s, int dim, int B, int n, double kbh, double centre, const double* dirs,
+                         c32* tables);
 void launch_plane_wave(hipStream_t s, int dim, int B, int n, const float* fplane, const c32* tables, c32* rhs,
                        c32* uin);
 void launch_grad_n(hipStream_t s, int dim, int B, int n_e, int w, int n, const c32* uin, const c32* u,
@@ -250,6 +253,14 @@ void launch_setup_fine(hipStream_t s, const SetupFineArgs& a);
 // kappa c carried as float-float (hi, lo planes)
 void launch_setup_coarse(hipStream_t s, int dim, int nf, int nc, const c32* kcf, const c32* kcflo, float omega,
                          c32* kcc, c32* kcclo, c32* wdc);
+
+// Inverse of the coarsest K'_l (complex double, dense, padded to coarse_inverse_rows(Nc) rows)
+// without pivoting, written as float to minvT; kc, kclo: kappa c of the level as float-float,
+// ghost_im: k_b h_l.  work: coarse_inverse_work(Nc) entries.  *flag (device): 0 where every
+// row is finite and diagonally dominant, else 1 and minvT is not to be used.
+size_t coarse_inverse_work(int Nc);
+void launch_coarse_inverse(hipStream_t s, int dim, int nl, const c32* kc, const c32* kclo, double ghost_im,
+                           double2* work, c32* minvT, int* flag);
 
 // Fixed device scratch of the allocation-free data residual (k_static.hip): per-device
 // address from hipGetSymbolAddress (static_scratch_init once per device, with it current),

@@ -1,6 +1,6 @@
 """The levels of a cycle at the sizes where their kernels or launches change: the two-launch
-form of the coarse levels (coarsest grids of more than 128 points) against the FP64 oracle,
-the march lengths of the 3D legs against each other."""
+form of the coarse levels (coarsest grids of more than 128 points) and the coarsest inverse
+against the FP64 oracle, the march lengths of the 3D legs against each other."""
 from __future__ import annotations
 
 import numpy as np
@@ -48,3 +48,24 @@ def test_march_lengths_agree(n, B):
         one = ctx.precondition(r)
         many = ctx.precondition(r.expand(B, *ctx.grid_shape()).contiguous())
         assert bool((many == one).all())
+
+
+# coarsest grids of 25 (one 32-point block), 36, 256 (whole blocks), 529, 64 and 343 points
+@pytest.mark.parametrize("n, levels, d", [(49, 5, 2), (65, 5, 2), (105, 4, 2), (161, 4, 2), (9, 4, 3), (33, 4, 3)])
+def test_coarsest_inverse_matches_oracle(n, levels, d):
+    nmap = medium(n, seed=8, d=d)
+    prob = oracle_problem(nmap, levels=levels)
+    hier = Hierarchy(prob)
+    diag = hier.K[-1].diagonal()
+    assert np.all(np.abs(diag) > np.asarray(abs(hier.K[-1]).sum(axis=1)).ravel() - np.abs(diag))  # inverted on the GPU
+    shape = (hier.sizes[-1],) * d
+    r = synth.complex_field((5, *shape), 72)
+    other = medium(n, seed=9, d=d)
+    with gpu_context(other, levels=levels, max_batch=5) as ctx:
+        import torch
+
+        ctx.update_n(torch.tensor(nmap, dtype=torch.float32, device="cuda"))
+        z = to_np(ctx.coarse_solve(to_dev(r)))
+    ref = np.stack([hier.coarse_lu.solve(ri.ravel()).reshape(shape) for ri in r])
+    # the 64-bit inverse rounded to 32 bits and a single-precision product of a well-conditioned matrix
+    assert rel(z, ref) < 1e-6
