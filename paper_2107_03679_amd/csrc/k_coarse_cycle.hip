@@ -248,31 +248,28 @@ __global__ __launch_bounds__(CC_NT) void k_coarse_cycle_lds(CoarseCycleArgs a) {
 
 // ---- the same cycle in two launches, for coarsest grids whose product is the long part ----
 // One workgroup per right-hand side reads the whole inverse (8 Nc^2 bytes: 1.3 MB at 20^2)
-// through one CU, 26-40 us of the 37-53 us the single launch takes.  Here CD_ROWS rows of
-// the product belong to one workgroup: ceil(Nc / CD_ROWS) workgroups per right-hand side
-// each repeat the down part (a few points per thread, in LDS) and form their rows, with
-// their slice of the inverse loaded into registers before the down part, so that it is
-// there when the coarsest right-hand side is.  The up part is a second launch (it needs
-// every row).  Whole solves at 1e-7, single launch against two: 128^2 x 1 (22^2 coarsest)
-// 18.9 -> 11.2 ms, 203^2 x 7 FGMRES (17^2) 43.0 -> 33.8, a gradient at 256^2 x 32 (20^2)
-// 159 -> 106, 64^3 x 8 (8^3, whose vectors did not fit the single launch's LDS) 91.8 -> 64.6.
-constexpr int CD_ROWS = 32, CD_GRP = CC_NT / CD_ROWS, CD_MK = 20, CD_MP = 4;
+// through one CU, 26-40 us of the 37-53 us the single launch takes.  Here 32 or 64 rows of
+// the product belong to one workgroup: the workgroups of a right-hand side each repeat the
+// down part (a few points per thread, in LDS) and form their rows, with their slice of the
+// inverse loaded into registers before the down part, so that it is there when the coarsest
+// right-hand side is.  The up part is a second launch (it needs every row).  32 rows while
+// those workgroups are at most one per CU, else 64, which repeats the down part less (down
+// launch at 20^2 x 32: 11.6 us with 32 rows, 9.3 with 64).  Whole solves at 1e-7, single
+// launch against two: 128^2 x 1 (22^2 coarsest) 18.9 -> 11.2 ms, 203^2 x 7 FGMRES (17^2) 43.0
+// -> 32.9, a gradient at 256^2 x 32 (20^2) 159 -> 99, 64^3 x 8 (8^3, whose vectors did not fit
+// the single launch's LDS) 91.8 -> 64.6.
+constexpr int CD_MAXN = 640, CD_MP = 4;
 
-template <int DIM>
+// MK: entries of a row per thread, ceil(Nc / CD_GRP) rounded up
+template <int DIM, int CD_ROWS, int MK>
 __global__ __launch_bounds__(CC_NT) void k_coarse_down_rows(CoarseCycleArgs a) {
+  constexpr int HALF = CD_ROWS / 32;  // columns per thread and pass: 1, or 2 with 64 rows
   extern __shared__ c32 lds[];
   const int b = blockIdx.y;
   if (a.active && !a.active[b]) return;
   const float om = a.omega;
   const int tid = threadIdx.x, Nc = (int)a.lv[a.L - 1].N, row0 = blockIdx.x * CD_ROWS;
-  const int rr = tid % CD_ROWS, g = tid / CD_ROWS, row = row0 + rr;
-  // this thread's entries of the inverse: row `row`, columns g, g + CD_GRP, ...
-  c32 mk[CD_MK];
-#pragma unroll
-  for (int u = 0; u < CD_MK; ++u) {
-    const int k = min(g + u * CD_GRP, Nc - 1);
-    mk[u] = a.minvT[(long long)k * Nc + min(row, Nc - 1)];
-  }
+  const int rr = tid % CD_ROWS, row = row0 + rr;
   c32* se = lds;                      // W r of the current level; at the end the coarsest right-hand side
   c32* st = lds + (int)a.lv[a.lp].N;  // its residual
   c32 r[CD_MP], w[CD_MP];
@@ -286,6 +283,15 @@ __global__ __launch_bounds__(CC_NT) void k_coarse_down_rows(CoarseCycleArgs a) {
       w[i] = F.wd[p];
     }
   }
+  // this thread's entries of the inverse: row `row`, columns g + 32 u (g the column group; with
+  // 64 rows the two groups that two threads of a wavefront hold with 32, so that the sums are
+  // the same); issued after the loads above, which the first stage waits for, and used last
+  c32 mk[MK];
+  const int g = tid / CD_ROWS * HALF;
+  auto column = [&](int u) { return g + u % HALF + u / HALF * 32; };
+#pragma unroll
+  for (int u = 0; u < MK; ++u) mk[u] = a.minvT[(long long)min(column(u), Nc - 1) * Nc + min(row, Nc - 1)];
+  __builtin_amdgcn_sched_barrier(0);
   for (int l = a.lp; l < a.L - 1; ++l) {
     const CoarseLevel& F = a.lv[l];
     const CoarseLevel& C = a.lv[l + 1];
@@ -318,15 +324,16 @@ __global__ __launch_bounds__(CC_NT) void k_coarse_down_rows(CoarseCycleArgs a) {
     // the next level's first stage writes se (last read before the barrier above)
   }
   __syncthreads();
-  c32 acc = make_float2(0.f, 0.f);
+  c32 part[HALF];
 #pragma unroll
-  for (int u = 0; u < CD_MK; ++u) {
-    const int k = g + u * CD_GRP;
-    if (k < Nc) acc = cfma(mk[u], se[k], acc);
-  }
-  // a wavefront holds two column groups of the 32 rows; then 16 partial sums per row
-  acc.x += __shfl_xor(acc.x, CD_ROWS, HELM_WAVE);
-  acc.y += __shfl_xor(acc.y, CD_ROWS, HELM_WAVE);
+  for (int q = 0; q < HALF; ++q) part[q] = make_float2(0.f, 0.f);
+#pragma unroll
+  for (int u = 0; u < MK; ++u)
+    if (column(u) < Nc) part[u % HALF] = cfma(mk[u], se[column(u)], part[u % HALF]);
+  // a wavefront holds two column groups; then 16 partial sums per row
+  c32 acc = part[0];
+  if (HALF == 2) acc = cadd(acc, part[HALF - 1]);
+  else acc = cadd(acc, make_float2(__shfl_xor(acc.x, 32, HELM_WAVE), __shfl_xor(acc.y, 32, HELM_WAVE)));
   c32* red = st;  // free since the barrier above
   if (tid % HELM_WAVE < CD_ROWS) red[(tid / HELM_WAVE) * CD_ROWS + rr] = acc;
   __syncthreads();
@@ -410,24 +417,37 @@ size_t coarse_cycle_lds_bytes(const CoarseCycleArgs& a) {
 // the threads' registers; one launch below (37^2 / 10^2 x 60: 14.3 us in one).
 bool coarse_cycle_split(const CoarseCycleArgs& a) {
   const long long Nc = a.lv[a.L - 1].N, Nf = a.lv[a.lp].N;
-  return a.lp < a.L - 1 && Nc > 128 && Nc <= CD_GRP * CD_MK && Nf <= CC_NT * CD_MP;
+  return a.lp < a.L - 1 && Nc > 128 && Nc <= CD_MAXN && Nf <= CC_NT * CD_MP;
 }
+
+namespace {
+template <int DIM, int ROWS, int M0, int M1, int M2, int M3>
+void coarse_down_rows(hipStream_t s, int B, size_t lds, int Nc, const CoarseCycleArgs& a) {
+  const dim3 grid((Nc + ROWS - 1) / ROWS, B);
+  const int mk = (Nc * ROWS + CC_NT - 1) / CC_NT;
+  if (mk <= M0) hipLaunchKernelGGL((k_coarse_down_rows<DIM, ROWS, M0>), grid, dim3(CC_NT), lds, s, a);
+  else if (mk <= M1) hipLaunchKernelGGL((k_coarse_down_rows<DIM, ROWS, M1>), grid, dim3(CC_NT), lds, s, a);
+  else if (mk <= M2) hipLaunchKernelGGL((k_coarse_down_rows<DIM, ROWS, M2>), grid, dim3(CC_NT), lds, s, a);
+  else hipLaunchKernelGGL((k_coarse_down_rows<DIM, ROWS, M3>), grid, dim3(CC_NT), lds, s, a);
+}
+template <int DIM>
+void coarse_down(hipStream_t s, int B, size_t lds, int Nc, const CoarseCycleArgs& a) {
+  if ((long long)B * ((Nc + 31) / 32) <= 256) coarse_down_rows<DIM, 32, 8, 13, 16, 20>(s, B, lds, Nc, a);
+  else coarse_down_rows<DIM, 64, 16, 26, 32, 40>(s, B, lds, Nc, a);
+}
+}  // namespace
 
 void launch_coarse_cycle(hipStream_t s, int B, const CoarseCycleArgs& a) {
   if (coarse_cycle_split(a)) {
     const int Nc = (int)a.lv[a.L - 1].N, Nf = (int)a.lv[a.lp].N;
-    // down: two vectors of the finest level (the second at least the 16 x 32 partial sums);
+    // down: two vectors of the finest level (the second at least the 16 partial sums per row);
     // up: one, and one of the level below
-    const size_t down = (size_t)(Nf + std::max(Nf, CC_NT / HELM_WAVE * CD_ROWS)) * sizeof(c32);
+    const size_t down = (size_t)(Nf + std::max(Nf, CC_NT)) * sizeof(c32);
     const size_t up = (size_t)(Nf + a.lv[a.lp + 1].N) * sizeof(c32);
-    const dim3 rows((Nc + CD_ROWS - 1) / CD_ROWS, B);
-    if (a.dim == 2) {
-      hipLaunchKernelGGL(k_coarse_down_rows<2>, rows, dim3(CC_NT), down, s, a);
-      hipLaunchKernelGGL(k_coarse_up_rows<2>, dim3(B), dim3(CC_NT), up, s, a);
-    } else {
-      hipLaunchKernelGGL(k_coarse_down_rows<3>, rows, dim3(CC_NT), down, s, a);
-      hipLaunchKernelGGL(k_coarse_up_rows<3>, dim3(B), dim3(CC_NT), up, s, a);
-    }
+    if (a.dim == 2) coarse_down<2>(s, B, down, Nc, a);
+    else coarse_down<3>(s, B, down, Nc, a);
+    if (a.dim == 2) hipLaunchKernelGGL(k_coarse_up_rows<2>, dim3(B), dim3(CC_NT), up, s, a);
+    else hipLaunchKernelGGL(k_coarse_up_rows<3>, dim3(B), dim3(CC_NT), up, s, a);
     return;
   }
   const size_t lds = coarse_cycle_lds_bytes(a);

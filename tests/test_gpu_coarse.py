@@ -22,6 +22,9 @@ pytestmark = pytest.mark.gpu
     (77, 3, 2, 1),   # 93, 47, 24^2: 576 points, the last row block half full
     (5, 3, 3, 2),    # 21, 11, 6^3
     (13, 3, 3, 5),   # 29, 15, 8^3: 15^3 points in four passes of the workgroup
+    (29, 3, 2, 60),  # over 256 workgroups of 32 rows: 64 rows each
+    (77, 3, 2, 20),
+    (13, 3, 3, 20),
 ])
 def test_split_coarse_cycle_matches_oracle(n, levels, d, B):
     nmap = medium(n, seed=5, d=d)
