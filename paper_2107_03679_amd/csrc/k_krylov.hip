@@ -773,20 +773,30 @@ __global__ __launch_bounds__(NT) void k_sstep_gram(int nrhs, KrylovArgs k, Level
   }
 }
 
-// Per right-hand side (one wavefront): reduce the Gram partials (FP64, fixed
-// order), Cholesky G = R^H R, Givens rotations of the Hessenberg R[:, 1:],
-// the residual estimate of every leading size, and the least-squares solution
-// for the smallest size that meets the inner tolerance (else all usable
-// columns).  A column whose Cholesky pivot vanishes (the Krylov space is
-// exhausted to working precision) ends the usable basis there.
+// Value of a double in lane l (the same for the whole wavefront).
+__device__ __forceinline__ double lane_d(double v, int l) {
+  return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), l), __builtin_amdgcn_readlane(__double2loint(v), l));
+}
+__device__ __forceinline__ double2 lane_z(double2 v, int l) { return make_double2(lane_d(v.x, l), lane_d(v.y, l)); }
+
+// Per right-hand side: reduce the Gram partials (FP64, fixed order), then in one wavefront
+// the Cholesky factor G = R^H R, Givens rotations of the Hessenberg R[:, 1:], the residual
+// estimate of every leading size, and the least-squares solution for the smallest size that
+// meets the inner tolerance (else all usable columns).  A column whose Cholesky pivot
+// vanishes (the Krylov space is exhausted to working precision) ends the usable basis there.
+// Lane l holds column l of R, later column l - 1 of the Hessenberg, in registers: the row a
+// step needs from another column comes through readlane, every lane forms the rotations for
+// itself.  In a single thread with its arrays in LDS these ~300 dependent complex operations
+// were 38 of the kernel's 41 us (128^2 x 1), at 512^2 x 60 the partials (three threads per
+// entry) 15 more: 41 -> 12 us and 52 -> 19 (256^2 x 32: 47 -> 17).
+constexpr int SNT = 1024;
 template <int M>
-__global__ __launch_bounds__(NT) void k_sstep_solve(KrylovArgs k, const double2* part) {
-  constexpr int NV = M + 1, NE = NV * (NV + 1) / 2, S = NT / NE;
-  static_assert(S >= 1, "one thread per entry at least");
+__global__ __launch_bounds__(SNT) void k_sstep_solve(KrylovArgs k, const double2* part) {
+  constexpr int NV = M + 1, NE = NV * (NV + 1) / 2, S = SNT / NE;
+  static_assert(S >= 1 && NV <= HELM_WAVE, "one thread per entry, one lane per column");
   __shared__ double2 G[NE];
   __shared__ double2 red[S][NE];
-  __shared__ double2 R[NV][NV];  // Cholesky factor (LDS: a per-thread array of this size would spill)
-  __shared__ double2 yd[M];
+  __shared__ double2 Hs[M][M + 1];
   const int b = blockIdx.x;
   if (!k.active[b]) return;
   // thread (e, s) sums the partials of entry e over blocks s, s + S, ... (four loads in
@@ -820,67 +830,59 @@ __global__ __launch_bounds__(NT) void k_sstep_solve(KrylovArgs k, const double2*
     G[threadIdx.x] = g;
   }
   __syncthreads();
-  if (threadIdx.x != 0) return;
-  const int m = k.m;
+  if (threadIdx.x >= HELM_WAVE) return;
+  const int lane = threadIdx.x, m = k.m;
   // packed index of (i, j), i <= j
   auto gi = [](int i, int j) { return i * NV - i * (i - 1) / 2 + (j - i); };
+  double2 R[NV];  // this lane's column, rows 0 .. lane
+  double gdiag = 0.0;
+#pragma unroll
+  for (int i = 0; i < NV; ++i) R[i] = lane >= i && lane < NV ? G[gi(i, lane)] : make_double2(0.0, 0.0);
+#pragma unroll
+  for (int i = 0; i < NV; ++i)
+    if (lane == i) gdiag = R[i].x;
   int keep = NV;  // usable leading columns of W
   bool finite = true;
-  for (int j = 0; j < NV && keep == NV; ++j) {
-    double d = G[gi(j, j)].x;
-    const double gjj = d;
-    for (int i = 0; i < j; ++i) d -= R[i][j].x * R[i][j].x + R[i][j].y * R[i][j].y;
+#pragma unroll
+  for (int j = 0; j < NV; ++j) {
+    if (keep < NV) continue;  // uniform, as every branch on d below
+#pragma unroll
+    for (int i = 0; i < j; ++i) {
+      const double2 t = zmul(zconj(lane_z(R[i], j)), R[i]);
+      R[j].x -= t.x;
+      R[j].y -= t.y;
+    }
+    const double d = lane_d(R[j].x, j), gjj = lane_d(gdiag, j);
     if (!isfinite(d) || !isfinite(gjj)) {
       finite = false;
       keep = j;
-      break;
-    }
-    if (!(d > 1e-13 * gjj) || !(gjj > 0.0)) {
+    } else if (!(d > 1e-13 * gjj) || !(gjj > 0.0)) {
       keep = j;
-      break;
-    }
-    const double rjj = sqrt(d);
-    R[j][j] = make_double2(rjj, 0.0);
-    for (int l = j + 1; l < NV; ++l) {
-      double2 v = G[gi(j, l)];
-      for (int i = 0; i < j; ++i) {
-        const double2 t = zmul(zconj(R[i][j]), R[i][l]);
-        v.x -= t.x;
-        v.y -= t.y;
-      }
-      R[j][l] = make_double2(v.x / rjj, v.y / rjj);
+    } else {
+      const double rjj = sqrt(d);
+      R[j].x = lane == j ? rjj : R[j].x / rjj;
+      R[j].y = lane == j ? 0.0 : R[j].y / rjj;
     }
   }
   const int mm = keep - 1;  // usable preconditioned directions
-  k.iters[b] += M;           // preconditioner applications performed
+  if (lane == 0) k.iters[b] += M;  // preconditioner applications performed
   if (!finite || mm < 1) {
-    k.status[b] = HELM_STATUS_BREAKDOWN_DEV;
-    k.jcount[b] = 0;
-    k.active[b] = 0;
+    if (lane == 0) {
+      k.status[b] = HELM_STATUS_BREAKDOWN_DEV;
+      k.jcount[b] = 0;
+      k.active[b] = 0;
+    }
     return;
   }
-  // the rotated Hessenberg, rotations and right-hand side stay in LDS (a single
-  // thread's chain of dependent global accesses would dominate the kernel)
-  __shared__ double2 H[(M + 1) * M];
-  __shared__ double cs[M];
-  __shared__ double2 sn[M];
-  __shared__ double2 g[M + 1];
-  const double rn = 1.0 / (double)k.vs[b * (m + 1)];
-  for (int i = 0; i <= m; ++i) g[i] = make_double2(0.0, 0.0);
-  g[0] = make_double2(rn * R[0][0].x, 0.0);
+  // column c of the Hessenberg: R[0 .. c + 1] of lane c + 1; rotation c acts on rows c, c + 1
+  const double rn = 1.0 / (double)k.vs[b * (m + 1)], tol = k.tol[b];
+  double2 gj = make_double2(rn * lane_d(R[0].x, 0), 0.0), s = make_double2(0.0, 0.0);  // lane i: right-hand side i
   int kstar = mm;
-  for (int col = 0; col < mm; ++col) {
-    // column col of the Hessenberg: R[0..col+1][col+1]
-    for (int i = 0; i <= col + 1; ++i) H[i * m + col] = R[i][col + 1];
-    for (int i = 0; i < col; ++i) {
-      const double2 a = H[i * m + col], c2 = H[(i + 1) * m + col];
-      const double2 t1 = zmul(sn[i], c2);
-      const double2 t2 = zmul(zconj(sn[i]), a);
-      H[i * m + col] = make_double2(cs[i] * a.x + t1.x, cs[i] * a.y + t1.y);
-      H[(i + 1) * m + col] = make_double2(cs[i] * c2.x - t2.x, cs[i] * c2.y - t2.y);
-    }
-    const double2 a = H[col * m + col];
-    const double2 hb = H[(col + 1) * m + col];
+  bool stop = false;
+#pragma unroll
+  for (int c = 0; c < M; ++c) {
+    if (c >= mm || stop) continue;
+    const double2 a = lane_z(R[c], c + 1), hb = lane_z(R[c + 1], c + 1);
     const double aa = zabs(a), bb = zabs(hb);
     double cr;
     double2 sv;
@@ -889,30 +891,60 @@ __global__ __launch_bounds__(NT) void k_sstep_solve(KrylovArgs k, const double2*
       sv = make_double2(0.0, 0.0);
     } else if (aa == 0.0) {
       cr = 0.0;
-      sv = zconj(make_double2(hb.x / bb, hb.y / bb));
+      sv = make_double2(hb.x / bb, -hb.y / bb);
     } else {
       const double rho = hypot(aa, bb);
       cr = aa / rho;
       const double2 ph = make_double2(a.x / aa, a.y / aa);
       sv = zmul(ph, make_double2(hb.x / rho, -hb.y / rho));  // (a/|a|) conj(hb) / rho
     }
-    cs[col] = cr;
-    sn[col] = sv;
-    const double2 t = zmul(sv, hb);
-    H[col * m + col] = make_double2(cr * a.x + t.x, cr * a.y + t.y);
-    H[(col + 1) * m + col] = make_double2(0.0, 0.0);
-    const double2 gj = g[col];
-    const double2 t2 = zmul(zconj(sv), gj);
-    g[col + 1] = make_double2(-t2.x, -t2.y);
-    g[col] = make_double2(cr * gj.x, cr * gj.y);
-    if (zabs(g[col + 1]) <= k.tol[b]) {
-      kstar = col + 1;
-      break;
+    const double2 t1 = zmul(sv, R[c + 1]), t2 = zmul(zconj(sv), R[c]);
+    R[c] = make_double2(cr * R[c].x + t1.x, cr * R[c].y + t1.y);
+    R[c + 1] = make_double2(cr * R[c + 1].x - t2.x, cr * R[c + 1].y - t2.y);
+    const double2 t3 = zmul(zconj(sv), gj);
+    if (lane == c) {
+      s.x = cr * gj.x;
+      s.y = cr * gj.y;
+    }
+    gj = make_double2(-t3.x, -t3.y);
+    if (zabs(gj) <= tol) {
+      kstar = c + 1;
+      stop = true;
     }
   }
-  k.jcount[b] = kstar;
-  k.active[b] = 0;
-  back_substitute(k, b, kstar, yd, H, g);
+  // back substitution, column by column: lane i keeps row i of the triangle
+#pragma unroll
+  for (int i = 0; i < M; ++i)
+    if (lane >= 1 && lane <= M) Hs[i][lane - 1] = R[i];
+  __threadfence_block();  // one wavefront: the stores above are read back below
+  double2 row[M];
+#pragma unroll
+  for (int l = 0; l < M; ++l) row[l] = Hs[min(lane, M - 1)][l];
+  double2 dg = make_double2(1.0, 0.0), y = make_double2(0.0, 0.0);
+#pragma unroll
+  for (int l = 0; l < M; ++l)
+    if (lane == l) {
+      dg.x = row[l].x;
+      dg.y = row[l].y;
+    }
+  const double den = dg.x * dg.x + dg.y * dg.y;
+#pragma unroll
+  for (int l = M - 1; l >= 0; --l) {
+    if (l >= kstar) continue;
+    const double2 q = make_double2((s.x * dg.x + s.y * dg.y) / den, (s.y * dg.x - s.x * dg.y) / den);
+    if (lane == l) {
+      y.x = q.x;
+      y.y = q.y;
+    }
+    const double2 t = zmul(row[l], lane_z(q, l));
+    s.x -= t.x;
+    s.y -= t.y;
+  }
+  if (lane < m) k.y[b * m + lane] = make_float2((float)y.x, (float)y.y);
+  if (lane == 0) {
+    k.jcount[b] = kstar;
+    k.active[b] = 0;
+  }
 }
 
 __global__ void k_status_init(KrylovArgs k, int B) {
@@ -1174,7 +1206,7 @@ namespace {
 template <int M>
 void sstep_tail(hipStream_t s, int B, const KrylovArgs& k, const LevelArgs& fine, double2* part) {
   hipLaunchKernelGGL(k_sstep_gram<M>, dim3(B * k.nblk), dim3(NT), 0, s, B, k, fine, part);
-  hipLaunchKernelGGL(k_sstep_solve<M>, dim3(B), dim3(NT), 0, s, k, (const double2*)part);
+  hipLaunchKernelGGL(k_sstep_solve<M>, dim3(B), dim3(SNT), 0, s, k, (const double2*)part);
 }
 }  // namespace
 
