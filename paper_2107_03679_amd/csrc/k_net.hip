@@ -52,28 +52,6 @@ __device__ __forceinline__ const bf16* src_ptr(const bf16* in_img, const bf16* u
   return in_img + ((zc * H + yc) * W + xc) * s.in_ct + (ci0 - s.cup);
 }
 
-// one input channel ci of pixel (img, z, y, x) inside the layer, the value the staging gives
-template <int NDIM>
-__device__ __forceinline__ float fetch1(const NetSrc& s, long long img, int D, int H, int W, int z, int y, int x,
-                                        int ci) {
-  if (ci < s.cup) {
-    const int Du = NDIM == 3 ? (D + 1) / 2 : 1, Hu = (H + 1) / 2, Wu = (W + 1) / 2;
-    return (float)s.up[(((img * Du + (z >> 1)) * Hu + (y >> 1)) * Wu + (x >> 1)) * s.up_ct + ci];
-  }
-  const int c = ci - s.cup;
-  if (!s.pool) return (float)s.in[(((img * D + z) * H + y) * W + x) * s.in_ct + s.in_off + c];
-  const int Ds = NDIM == 3 ? s.Ds : 1;
-  float acc = 0.f;
-  for (int e = 0; e < (NDIM == 3 ? 2 : 1); ++e)
-    for (int a = 0; a < 2; ++a)
-      for (int b = 0; b < 2; ++b) {
-        const int zz = NDIM == 3 ? 2 * z + e : 0, yy = 2 * y + a, xx = 2 * x + b;
-        if (zz < Ds && yy < s.Hs && xx < s.Ws)
-          acc += (float)s.in[(((img * Ds + zz) * s.Hs + yy) * s.Ws + xx) * s.in_ct + s.in_off + c];
-      }
-  return (float)(bf16)((NDIM == 3 ? 0.125f : 0.25f) * acc);
-}
-
 // ---------------------------------------------------------------- conv, LDS-tiled (MFMA)
 // Block = TH x TW output pixels of one image plane, all output channels (NCO tiles
 // of 16).  The (TH + 2) x (TW + 2) input halo tile (in 3D: three planes of it,
@@ -1108,137 +1086,6 @@ __global__ __launch_bounds__(256) void k_conv3c(ConvArgs a) {
   }
 }
 
-// ---------------------------------------------------------------- weight gradient (MFMA)
-// dW[co][k] = sum_p in[p + shift(tap(k))][ci(k)] * g[p][co]: a GEMM over pixels.
-// Block (k tile of 16, channel tile of 16, pixel chunk); each wavefront takes a
-// quarter of the chunk, the four partial tiles are summed in LDS and written
-// to part[chunk][co][k] (reduced in a fixed order by k_wgrad_reduce).
-template <int NDIM>
-__global__ __launch_bounds__(256) void k_wgrad(WgradArgs a) {
-  constexpr int NT = NDIM == 3 ? 27 : 9;
-  __shared__ float red[4][16][17];
-  const int wave = threadIdx.x / 64, l = threadIdx.x % 64, gq = l / 16, i16 = l % 16;
-  const int kt = blockIdx.x, ct = blockIdx.y, chunk = blockIdx.z;
-  const int D = NDIM == 3 ? a.D : 1;
-  const long long P = (long long)a.nimg * D * a.H * a.W;
-  const long long p_begin = (long long)chunk * a.chunk + (long long)wave * (a.chunk / 4);
-  const long long p_end = min(p_begin + a.chunk / 4, P);
-  const int krow = kt * 16 + i16;                  // A row of this lane
-  const int tap = krow / a.cin, ci = krow - tap * a.cin;
-  const int dz = NDIM == 3 ? tap / 9 - 1 : 0, tp = NDIM == 3 ? tap % 9 : tap;
-  const int dy = tp / 3 - 1, dx = tp % 3 - 1;
-  const int co = ct * 16 + i16;                    // B column of this lane
-  f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-  // pixel (img, pz, py, px) of this lane's first element, advanced by one pixel per
-  // element and by 32 per step instead of divided out of p each time
-  long long img0;
-  int px0, py0, pz0;
-  {
-    const long long p = p_begin + 8 * gq;
-    px0 = (int)(p % a.W);
-    const long long r = p / a.W;
-    py0 = (int)(r % a.H);
-    const long long r2 = r / a.H;
-    pz0 = NDIM == 3 ? (int)(r2 % D) : 0;
-    img0 = NDIM == 3 ? r2 / D : r2;
-  }
-  auto next_row = [&](int& py, int& pz, long long& img) {
-    if (++py == a.H) {
-      py = 0;
-      if (NDIM == 3 && ++pz < D) return;
-      pz = 0;
-      ++img;
-    }
-  };
-  for (long long pc = p_begin; pc < p_end; pc += 32) {
-    bf16x8 av, bv;
-    int px = px0, py = py0, pz = pz0;
-    long long img = img0;
-#pragma unroll
-    for (int v = 0; v < 8; ++v) {
-      const long long p = pc + 8 * gq + v;
-      float xa = 0.f, gb = 0.f;
-      if (p < p_end) {
-        const int zz = pz + dz, yy = py + dy, xx = px + dx;
-        if (tap < NT && zz >= 0 && zz < D && yy >= 0 && yy < a.H && xx >= 0 && xx < a.W)
-          xa = fetch1<NDIM>(a.src, img, D, a.H, a.W, zz, yy, xx, ci);
-        gb = (float)a.g[p * a.g_ct + co];
-      }
-      av[v] = (__bf16)xa;
-      bv[v] = (__bf16)gb;
-      if (++px == a.W) {
-        px = 0;
-        next_row(py, pz, img);
-      }
-    }
-    acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, bv, acc, 0, 0, 0);
-    px0 += 32;
-    while (px0 >= a.W) {
-      px0 -= a.W;
-      next_row(py0, pz0, img0);
-    }
-  }
-  // D[i][j]: i = k row (4 gq + r), j = co column (i16)
-#pragma unroll
-  for (int r = 0; r < 4; ++r) red[wave][4 * gq + r][i16] = acc[r];
-  __syncthreads();
-  const int i = threadIdx.x / 16, j = threadIdx.x % 16;  // 256 threads = 16 x 16 outputs
-  const float s = red[0][i][j] + red[1][i][j] + red[2][i][j] + red[3][i][j];
-  a.part[((long long)chunk * a.cout_pad + ct * 16 + j) * a.kpad + kt * 16 + i] = s;
-}
-
-__global__ void k_wgrad_reduce(int nchunk, int n, const float* part, float* dw) {
-  const int t = blockIdx.x * blockDim.x + threadIdx.x;
-  if (t >= n) return;
-  float s = 0.f;
-  for (int c = 0; c < nchunk; ++c) s += part[(long long)c * n + t];
-  dw[t] = s;
-}
-
-// db[co] = sum_p g[p][co], first stage: block `chunk` sums its pixels [chunk * n, ...)
-// into part[chunk][co]; thread t takes channel t % g_ct of every (256 / g_ct)-th pixel, so
-// a block reads consecutive 512-byte rows of g.  The chunk partials are then summed in
-// chunk order (k_wgrad_reduce): the same order on every call.  g_ct divides 256.
-__global__ __launch_bounds__(256) void k_bias_part(long long P, int n, const bf16* g, int g_ct, int cout,
-                                                   float* part) {
-  __shared__ float red[256];
-  const int c = threadIdx.x % g_ct, lane = threadIdx.x / g_ct, lanes = 256 / g_ct;
-  const long long p0 = (long long)blockIdx.x * n, p1 = min(p0 + n, P);
-  float s = 0.f;
-  long long p = p0 + lane;
-  // 16 loads in flight, added in the order of p
-  for (; p + 15 * lanes < p1; p += 16 * lanes) {
-    float v[16];
-#pragma unroll
-    for (int u = 0; u < 16; ++u) v[u] = (float)g[(p + u * lanes) * g_ct + c];
-#pragma unroll
-    for (int u = 0; u < 16; ++u) s += v[u];
-  }
-  for (; p < p1; p += lanes) s += (float)g[p * g_ct + c];
-  red[threadIdx.x] = s;
-  __syncthreads();
-  if (threadIdx.x < cout) {
-    float t = 0.f;
-    for (int k = 0; k < lanes; ++k) t += red[k * g_ct + threadIdx.x];
-    part[(long long)blockIdx.x * cout + threadIdx.x] = t;
-  }
-}
-
-// db[co] = sum_p g[p][co] in one block per channel (channel strides that do not divide 256)
-__global__ void k_bias_grad(long long P, const bf16* g, int g_ct, float* db) {
-  __shared__ float red[256];
-  const int co = blockIdx.x;
-  float s = 0.f;
-  for (long long p = threadIdx.x; p < P; p += 256) s += (float)g[p * g_ct + co];
-  red[threadIdx.x] = s;
-  __syncthreads();
-  for (int w = 128; w > 0; w >>= 1) {
-    if (threadIdx.x < w) red[threadIdx.x] += red[threadIdx.x + w];
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) db[co] = red[0];
-}
-
 // ---------------------------------------------------------------- elementwise
 // gm[p][c] = (c < creal) ? g[p][c] * (mask ? act[p][c] > 0 : 1) : 0, bf16 out (cpad channels)
 __global__ void k_grad_prep(long long P, const float* g, int g_ct, int g_off, const bf16* act, int act_ct,
@@ -1733,23 +1580,6 @@ void launch_conv3x3(hipStream_t s, const ConvArgs& a, int nco, int dim, bool gen
     case 6: conv_lds<6, 4, 32, 2>(s, a); break;
     case 8: conv_lds<8, 4, 32, 2>(s, a); break;
     default: break;
-  }
-}
-
-void launch_wgrad(hipStream_t s, const WgradArgs& a, int nchunk, float* dw, const bf16* g_for_bias, float* db,
-                  int cout_real) {
-  const dim3 grid(a.kpad / 16, a.cout_pad / 16, nchunk);
-  if (a.dim == 3) hipLaunchKernelGGL(k_wgrad<3>, grid, dim3(256), 0, s, a);
-  else hipLaunchKernelGGL(k_wgrad<2>, grid, dim3(256), 0, s, a);
-  const int n = a.cout_pad * a.kpad;
-  hipLaunchKernelGGL(k_wgrad_reduce, dim3(nb(n, 256)), dim3(256), 0, s, nchunk, n, a.part, dw);
-  const long long P = (long long)a.nimg * (a.dim == 3 ? a.D : 1) * a.H * a.W;
-  if (256 % a.g_ct == 0 && cout_real <= a.g_ct) {
-    // the weight partials are consumed by now (stream order): reuse the buffer
-    hipLaunchKernelGGL(k_bias_part, dim3(nchunk), dim3(256), 0, s, P, a.chunk, g_for_bias, a.g_ct, cout_real, a.part);
-    hipLaunchKernelGGL(k_wgrad_reduce, dim3(nb(cout_real, 256)), dim3(256), 0, s, nchunk, cout_real, a.part, db);
-  } else {
-    hipLaunchKernelGGL(k_bias_grad, dim3(cout_real), dim3(256), 0, s, P, g_for_bias, a.g_ct, db);
   }
 }
 

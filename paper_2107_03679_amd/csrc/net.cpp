@@ -71,7 +71,7 @@ struct NetBufs {
   float* rpart = nullptr;
   float *y = nullptr, *gy = nullptr, *g_d0 = nullptr, *g_cat0 = nullptr, *g_d1 = nullptr, *g_cat1 = nullptr,
         *g_d2 = nullptr, *g_cat2 = nullptr, *g_e3 = nullptr, *g_p = nullptr, *part = nullptr, *lpart = nullptr;
-  long long part_n = 0;
+  long long part_off[HELM_NET_LAYERS] = {0};
   int D[4] = {1, 1, 1, 1}, H[4] = {0}, W[4] = {0};
   long long P[4] = {0};
 };
@@ -105,7 +105,7 @@ struct helm_net {
 
 namespace {
 
-constexpr int WCHUNK = 4096;
+constexpr int kLevel[HELM_NET_LAYERS] = {0, 1, 2, 3, 2, 1, 0, 0};  // resolution of each layer
 
 void free_bufs(helm_net* n) {
   for (void* p : n->cur->bufs) hipFree(p);
@@ -123,6 +123,24 @@ void shape(helm_net* n, int nimg, int D0, int H0, int W0) {
     n->cur->W[l] = (n->cur->W[l - 1] + 1) / 2;
   }
   for (int l = 0; l < 4; ++l) n->cur->P[l] = (long long)nimg * n->cur->D[l] * n->cur->H[l] * n->cur->W[l];
+}
+
+// Weight-gradient plan of layer i at the current shape, nimg images
+WgradArgs wgrad_args(const helm_net* n, int i, int nimg) {
+  const NetLayer& L = n->L[i];
+  const int lvl = kLevel[i];
+  WgradArgs a{};
+  a.cin = L.cin_pad;
+  a.nimg = nimg;
+  a.D = n->cur->D[lvl];
+  a.H = n->cur->H[lvl];
+  a.W = n->cur->W[lvl];
+  a.dim = n->dim;
+  a.g_ct = L.cout_pad;
+  a.kpad = L.kpad;
+  a.cout_pad = L.cout_pad;
+  wgrad_plan(a);
+  return a;
 }
 
 // Buffers for up to nimg images of D0 x H0 x W0 (reallocated only when they do not fit).
@@ -156,14 +174,13 @@ void ensure(helm_net* n, int nimg, int D0, int H0, int W0, bool train) {
     n->cur->g_e3 = n->alloc<float>(P[3] * c[3], B);
     n->cur->g_p = n->alloc<float>(std::max({P[1] * c[0], P[2] * c[1], P[3] * c[2]}), B);
     n->cur->gm = n->alloc<bf16>(std::max({P[0] * c[0], P[1] * c[1], P[2] * c[2], P[3] * c[3]}), B);
-    long long pn = 0;
-    const int lvl[HELM_NET_LAYERS] = {0, 1, 2, 3, 2, 1, 0, 0};
+    long long pn = 0;  // every layer's partial sums, one after the other
     for (int i = 0; i < HELM_NET_LAYERS; ++i) {
-      const long long nch = (P[lvl[i]] + WCHUNK - 1) / WCHUNK;
-      pn = std::max(pn, nch * n->L[i].cout_pad * n->L[i].kpad);
+      n->cur->part_off[i] = pn;
+      const WgradArgs a = wgrad_args(n, i, nimg);
+      pn += a.nchunk * a.part_stride;
     }
     n->cur->part = n->alloc<float>(pn, B);
-    n->cur->part_n = pn;
     n->cur->lpart = n->alloc<float>(loss_partials(P[0] * 2), B);
     n->cur->q = n->alloc<float2>(P[0], B);
     n->cur->rpart = n->alloc<float>(loss_partials(P[0]), B);
@@ -243,24 +260,17 @@ void conv_back(helm_net* n, int i, int lvl, float* gin, int g_ct) {
   launch_conv3x3(n->s, a, wb_rows(L) / 16, n->dim, n->generic_conv);
 }
 
-void wgrad(helm_net* n, int i, const NetSrc& src, int lvl) {
+// partial sums of layer i's gradients; the plan of fewer images than the buffers hold needs no
+// more of them
+void wgrad(helm_net* n, int i, const NetSrc& src, WgradReduceArgs& red) {
   NetLayer& L = n->L[i];
-  WgradArgs a{};
+  WgradArgs a = wgrad_args(n, i, n->cur->cur_nimg);
   a.src = src;
-  a.cin = L.cin_pad;
-  a.nimg = n->cur->cur_nimg;
-  a.D = n->cur->D[lvl];
-  a.H = n->cur->H[lvl];
-  a.W = n->cur->W[lvl];
-  a.dim = n->dim;
   a.g = n->cur->gm;
-  a.g_ct = L.cout_pad;
-  a.kpad = L.kpad;
-  a.cout_pad = L.cout_pad;
-  a.chunk = WCHUNK;
-  a.part = n->cur->part;
-  const int nchunk = (int)((n->cur->P[lvl] + WCHUNK - 1) / WCHUNK);
-  launch_wgrad(n->s, a, nchunk, L.dw, n->cur->gm, L.db, L.cout);
+  a.part = n->cur->part + n->cur->part_off[i];
+  if (!launch_wgrad(n->s, a)) throw NetErr{hipErrorInvalidValue, "no weight-gradient kernel for this layer"};
+  red.L[red.n++] = WgradReduceLayer{a.part, a.part_stride, a.nchunk, L.cout_pad, L.cout, L.kpad,
+                                    n->ntaps * L.cin_pad, 0, L.dw, L.db};
 }
 
 void forward(helm_net* n) {
@@ -284,38 +294,40 @@ void backward(helm_net* n) {
   const long long* P = b.P;
   const int* c = n->ch;
   hipStream_t s = n->s;
+  WgradReduceArgs red{};
   // output layer (no ReLU): gy is the loss gradient of y
   launch_grad_prep(s, P[0], b.gy, 2, 0, nullptr, 0, 0, 2, n->L[OUT].cout_pad, b.gm);
-  wgrad(n, OUT, src_of(b.d0, c[0]), 0);
+  wgrad(n, OUT, src_of(b.d0, c[0]), red);
   conv_back(n, OUT, 0, b.g_d0, c[0]);
   // decoder
   launch_grad_prep(s, P[0], b.g_d0, c[0], 0, b.d0, c[0], 0, c[0], c[0], b.gm);
-  wgrad(n, B0, src_cat(b.d1, c[1], b.e0, c[0]), 0);
+  wgrad(n, B0, src_cat(b.d1, c[1], b.e0, c[0]), red);
   conv_back(n, B0, 0, b.g_cat0, c[1] + c[0]);
   launch_upsample_back(s, dim, N, b.D[0], b.H[0], b.W[0], c[1], b.g_cat0, c[1] + c[0], 0, b.g_d1);
   launch_grad_prep(s, P[1], b.g_d1, c[1], 0, b.d1, c[1], 0, c[1], c[1], b.gm);
-  wgrad(n, B1, src_cat(b.d2, c[2], b.e1, c[1]), 1);
+  wgrad(n, B1, src_cat(b.d2, c[2], b.e1, c[1]), red);
   conv_back(n, B1, 1, b.g_cat1, c[2] + c[1]);
   launch_upsample_back(s, dim, N, b.D[1], b.H[1], b.W[1], c[2], b.g_cat1, c[2] + c[1], 0, b.g_d2);
   launch_grad_prep(s, P[2], b.g_d2, c[2], 0, b.d2, c[2], 0, c[2], c[2], b.gm);
-  wgrad(n, B2, src_cat(b.e3, c[3], b.e2, c[2]), 2);
+  wgrad(n, B2, src_cat(b.e3, c[3], b.e2, c[2]), red);
   conv_back(n, B2, 2, b.g_cat2, c[3] + c[2]);
   launch_upsample_back(s, dim, N, b.D[2], b.H[2], b.W[2], c[3], b.g_cat2, c[3] + c[2], 0, b.g_e3);
   // encoder
   launch_grad_prep(s, P[3], b.g_e3, c[3], 0, b.e3, c[3], 0, c[3], c[3], b.gm);
-  wgrad(n, A3, src_pool(n, b.e2, c[2], 3), 3);
+  wgrad(n, A3, src_pool(n, b.e2, c[2], 3), red);
   conv_back(n, A3, 3, b.g_p, c[2]);
   launch_pool_back(s, dim, N, b.D[2], b.H[2], b.W[2], c[2], b.g_p, c[2], b.g_cat2, c[3] + c[2], c[3]);
   launch_grad_prep(s, P[2], b.g_cat2, c[3] + c[2], c[3], b.e2, c[2], 0, c[2], c[2], b.gm);
-  wgrad(n, A2, src_pool(n, b.e1, c[1], 2), 2);
+  wgrad(n, A2, src_pool(n, b.e1, c[1], 2), red);
   conv_back(n, A2, 2, b.g_p, c[1]);
   launch_pool_back(s, dim, N, b.D[1], b.H[1], b.W[1], c[1], b.g_p, c[1], b.g_cat1, c[2] + c[1], c[2]);
   launch_grad_prep(s, P[1], b.g_cat1, c[2] + c[1], c[2], b.e1, c[1], 0, c[1], c[1], b.gm);
-  wgrad(n, A1, src_pool(n, b.e0, c[0], 1), 1);
+  wgrad(n, A1, src_pool(n, b.e0, c[0], 1), red);
   conv_back(n, A1, 1, b.g_p, c[0]);
   launch_pool_back(s, dim, N, b.D[0], b.H[0], b.W[0], c[0], b.g_p, c[0], b.g_cat0, c[1] + c[0], c[1]);
   launch_grad_prep(s, P[0], b.g_cat0, c[1] + c[0], c[1], b.e0, c[0], 0, c[0], c[0], b.gm);
-  wgrad(n, A0, src_of(b.x0, 8), 0);
+  wgrad(n, A0, src_of(b.x0, 8), red);
+  launch_wgrad_reduce(s, red);
 }
 
 int fail(helm_net* n, int code, const std::string& msg) {

@@ -47,15 +47,31 @@ struct WgradArgs {
   const bf16* g;  // masked output gradient [P][g_ct]
   int g_ct;
   int kpad, cout_pad;
-  int chunk;    // pixels per block (multiple of 128)
-  float* part;  // [nchunk][cout_pad][kpad]
+  // set by wgrad_plan: tiles of pixels, blocks that share them, floats per block's partial sums
+  int ntile, nchunk;
+  long long part_stride;
+  float* part;  // [nchunk][part_stride]: [cout_pad][kpad] weights, [cout_pad] biases
+};
+// the reduction of every layer's partial sums
+struct WgradReduceLayer {
+  const float* part;
+  long long stride;
+  int nchunk, cout_pad, cout, kpad, kreal;  // kreal = taps * cin: entries past it are zero
+  int block0;
+  float *dw, *db;
+};
+struct WgradReduceArgs {
+  int n;
+  WgradReduceLayer L[8];
 };
 
 // 3x3 (dim 2) or 3x3x3 (dim 3) convolution, nco output tiles of 16 channels
 // generic: the channel-generic kernel even where a channel-specialised one exists
 void launch_conv3x3(hipStream_t s, const ConvArgs& a, int nco, int dim, bool generic);
-void launch_wgrad(hipStream_t s, const WgradArgs& a, int nchunk, float* dw, const bf16* g_for_bias, float* db,
-                  int cout_real);
+void wgrad_plan(WgradArgs& a);  // from dim, nimg, D, H, W, cin, cout_pad, kpad
+// partial sums of one layer's weight and bias gradients (false: not a layer of the networks)
+bool launch_wgrad(hipStream_t s, const WgradArgs& a);
+void launch_wgrad_reduce(hipStream_t s, WgradReduceArgs& a);
 void launch_grad_prep(hipStream_t s, long long P, const float* g, int g_ct, int g_off, const bf16* act, int act_ct,
                       int act_off, int creal, int cpad, bf16* gm);
 // pooling and upsampling adjoints at the fine resolution D x H x W (D = 1 in 2D)
