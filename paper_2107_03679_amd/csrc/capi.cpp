@@ -1783,7 +1783,7 @@ int helm_farfield_set(helm_ctx* c, int M, const double* sensors_host) {
   HELM_GUARD_BEGIN
   const long long Ni = npts(c->n, dim);
   if (M > c->ff_M) {
-    c->d_ffG = c->alloc<c32>((size_t)M * Ni);
+    c->d_ffG = c->alloc<c32>((size_t)M * Ni + 1);  // one more: the adjoint reads pixels in pairs
     c->d_ff_part = c->alloc<c32>((size_t)ff_splits(Ni) * c->o.max_batch * M);
     c->d_ff_iota = c->alloc<int>(M);
     std::vector<int> iota(M);
@@ -1874,8 +1874,6 @@ int helm_farfield_adjoint(helm_ctx* c, int B, const helm_c32* r, helm_c32* s_ext
   if (B < 1) return fail(c, HELM_EINVAL, "B must be >= 1");
   if (!c->ff_active_M) return fail(c, HELM_ESTATE, "no sensors: call helm_farfield_set first");
   HELM_GUARD_BEGIN
-  launch_zero(c->s, (long long)B * c->N0, (c32*)s_ext);
-  if (rhs_ext) launch_zero(c->s, (long long)B * c->N0, (c32*)rhs_ext);
   launch_ff_adjoint(c->s, c->dim, B, c->ff_active_M, c->ne, c->w, c->n, c->d_ffG, (const c32*)r, c->d_f, (c32*)s_ext,
                     (c32*)rhs_ext);
   HELM_GUARD_END("farfield_adjoint")

@@ -7,13 +7,24 @@
 //     g(x) = (j/4) H0^(1)(k_b |x|)  (2D),   e^{j k_b |x|} / (4 pi |x|)  (3D).
 // G~ [M][n^dim] is formed once per sensor set (2D: H0^(1) by cubic Hermite
 // interpolation in a host FP64 table of H0^(1) and its derivative; 3D: in
-// closed form in FP64), then applied as a split-K product and its adjoint.
+// closed form in FP64), then applied as a split-K product and its adjoint, both on the FP32
+// matrix cores (v_mfma_f32_16x16x4_f32, whose operands and sums are single precision): lane
+// (i16, g) = (l % 16, l / 16) gives row i16 of A and column i16 of B at k = g and holds rows
+// 4 g .. 4 g + 3 of column i16 of D.  A complex product is four real ones.
+#include <algorithm>
+
 #include "dev_common.h"
 #include "kernels.h"
 
 namespace {
 
-constexpr int TT = 32;  // tile edge of the products (32 x 32 outputs, 256 threads, 4 outputs each)
+typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f32x4;
+// 16 bytes at the 8-byte alignment of a complex field with rows of odd length
+typedef f32x4 f32x4_a8 __attribute__((aligned(8)));
+
+__device__ __forceinline__ f32x4 mfma4(float a, float b, f32x4 c) {
+  return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
+}
 
 __global__ void k_ff_matrix(int dim, int n, int M, const double* sens, double kbh, double h, const double2* tab,
                             double x0, double dx, int ntab, c32* G) {
@@ -69,87 +80,209 @@ __global__ void k_ff_source(int dim, int B, int ne, int w, int n, const float* f
   s[(long long)b * Ni + i] = cscale(u, fpl[p]);
 }
 
-// part[k][b][m] = sum over pixel chunk k of G[m][i] s[b][i]; block: 32 sensors x 32 RHS, chunk k
+// part[k][b][m] = sum over pixel chunk k of G[m][i] s[b][i].  A wavefront takes 16 sensors and
+// 16 BT right-hand sides, so that G, the large operand, is read once for up to 64 right-hand
+// sides: lane group g loads pixels 8 g .. 8 g + 7 of every 32 (64 bytes a lane, 256 a row), the
+// next 32 in flight meanwhile.  Bound by the FP32 rate (16 n^d B M operations) and G's 8 M
+// bytes per pixel.  180 sensors, 32 right-hand sides, 256^2: 167 us with 32 x 32 LDS tiles on
+// the vector units, which read five LDS values for four products, 44 us now (the matrix cores'
+// share 20).
+struct Px8 {
+  c32 v[8];
+};
+__device__ __forceinline__ Px8 load_px8(const c32* row, long long i, long long i1) {
+  Px8 o;
+  if (i + 8 <= i1) {
+    const f32x4_a8* q = reinterpret_cast<const f32x4_a8*>(row + i);
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const f32x4 t = q[u];
+      o.v[2 * u] = make_float2(t[0], t[1]);
+      o.v[2 * u + 1] = make_float2(t[2], t[3]);
+    }
+  } else {
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+      o.v[u] = make_float2(0.f, 0.f);
+      if (i + u < i1) o.v[u] = row[i + u];
+    }
+  }
+  return o;
+}
+
+template <int BT>
 __global__ __launch_bounds__(256) void k_ff_apply(int B, int M, long long Ni, long long chunk, const c32* G,
                                                    const c32* s, c32* part) {
-  __shared__ c32 sg[TT][TT + 1];
-  __shared__ c32 ss[TT][TT + 1];
-  const int m0 = blockIdx.x * TT, b0 = blockIdx.y * TT, k = blockIdx.z;
-  const long long i0 = (long long)k * chunk, i1 = i0 + chunk < Ni ? i0 + chunk : Ni;
-  const int tx = threadIdx.x % TT, ty = threadIdx.x / TT;  // ty in 0..7: rows ty, ty+8, ty+16, ty+24
-  c32 acc[4];
-  for (int q = 0; q < 4; ++q) acc[q] = make_float2(0.f, 0.f);
-  for (long long ib = i0; ib < i1; ib += TT) {
-    for (int q = 0; q < 4; ++q) {
-      const int row = ty + 8 * q;
-      const long long i = ib + tx;
-      const bool ok = i < i1;
-      sg[row][tx] = (ok && m0 + row < M) ? G[(long long)(m0 + row) * Ni + i] : make_float2(0.f, 0.f);
-      ss[row][tx] = (ok && b0 + row < B) ? s[(long long)(b0 + row) * Ni + i] : make_float2(0.f, 0.f);
+  const int lane = threadIdx.x % 64, i16 = lane % 16, g = lane / 16;
+  const int m0 = (blockIdx.x * 4 + threadIdx.x / 64) * 16, k = blockIdx.y, b0 = blockIdx.z * 16 * BT;
+  if (m0 >= M) return;
+  const long long i0 = (long long)k * chunk, i1 = min(i0 + chunk, Ni);
+  // rows past the last sensor or right-hand side repeat it; their sums are not stored
+  const c32* gr = G + (long long)min(m0 + i16, M - 1) * Ni;
+  const c32* sr[BT];
+#pragma unroll
+  for (int t = 0; t < BT; ++t) sr[t] = s + (long long)min(b0 + 16 * t + i16, B - 1) * Ni;
+  f32x4 re[BT], im[BT];
+#pragma unroll
+  for (int t = 0; t < BT; ++t) re[t] = im[t] = f32x4{0.f, 0.f, 0.f, 0.f};
+  Px8 gn = load_px8(gr, i0 + 8 * g, i1), sn[BT];
+#pragma unroll
+  for (int t = 0; t < BT; ++t) sn[t] = load_px8(sr[t], i0 + 8 * g, i1);
+  for (long long ib = i0; ib < i1; ib += 32) {
+    const Px8 gv = gn;
+    Px8 sv[BT];
+#pragma unroll
+    for (int t = 0; t < BT; ++t) sv[t] = sn[t];
+    if (ib + 32 < i1) {
+      gn = load_px8(gr, ib + 32 + 8 * g, i1);
+#pragma unroll
+      for (int t = 0; t < BT; ++t) sn[t] = load_px8(sr[t], ib + 32 + 8 * g, i1);
     }
-    __syncthreads();
-    // thread (tx, ty): sensor m0 + tx, RHS b0 + ty + 8 q
-    for (int t = 0; t < TT; ++t) {
-      const c32 gv = sg[tx][t];
-      for (int q = 0; q < 4; ++q) acc[q] = cfma(gv, ss[ty + 8 * q][t], acc[q]);
-    }
-    __syncthreads();
+#pragma unroll
+    for (int v = 0; v < 8; ++v)
+#pragma unroll
+      for (int t = 0; t < BT; ++t) {
+        re[t] = mfma4(gv.v[v].x, sv[t].v[v].x, re[t]);
+        im[t] = mfma4(gv.v[v].x, sv[t].v[v].y, im[t]);
+        re[t] = mfma4(-gv.v[v].y, sv[t].v[v].y, re[t]);
+        im[t] = mfma4(gv.v[v].y, sv[t].v[v].x, im[t]);
+      }
   }
-  for (int q = 0; q < 4; ++q) {
-    const int b = b0 + ty + 8 * q, m = m0 + tx;
-    if (b < B && m < M) part[((long long)k * B + b) * M + m] = acc[q];
+#pragma unroll
+  for (int t = 0; t < BT; ++t) {
+    const int b = b0 + 16 * t + i16;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int m = m0 + 4 * g + r;
+      if (b < B && m < M) part[((long long)k * B + b) * M + m] = make_float2(re[t][r], im[t][r]);
+    }
   }
 }
 
-// y[b][m] = sum over chunks (fixed order)
-__global__ void k_ff_reduce(int B, int M, int nsplit, const c32* part, c32* y) {
-  const int t = blockIdx.x * blockDim.x + threadIdx.x;
-  if (t >= B * M) return;
+// y[b][m] = sum over chunks (fixed order: four threads take every fourth chunk, eight loads in
+// flight)
+__global__ __launch_bounds__(256) void k_ff_reduce(int count, int nsplit, const c32* part, c32* y) {
+  __shared__ c32 red[4][64];
+  const int e = threadIdx.x % 64, q = threadIdx.x / 64, t = blockIdx.x * 64 + e;
   c32 a = make_float2(0.f, 0.f);
-  for (int k = 0; k < nsplit; ++k) a = cadd(a, part[(long long)k * B * M + t]);
-  y[t] = a;
+  if (t < count) {
+    int k = q;
+    for (; k + 28 < nsplit; k += 32) {
+      c32 v[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) v[u] = part[(long long)(k + 4 * u) * count + t];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) a = cadd(a, v[u]);
+    }
+    for (; k < nsplit; k += 4) a = cadd(a, part[(long long)k * count + t]);
+  }
+  red[q][e] = a;
+  __syncthreads();
+  if (q == 0 && t < count) y[t] = cadd(cadd(red[0][e], red[1][e]), cadd(red[2][e], red[3][e]));
 }
 
-// s_ext[b][p(i)] = sum_m conj(G[m][i]) r[b][m] on Omega (0 in the layer), rhs_ext = f s_ext;
-// block: 32 pixels x 32 RHS, sensors in tiles of 32
+// s_ext[b][p(i)] = sum_m conj(G[m][i]) r[b][m] on Omega, rhs_ext = f s_ext (the layer is zeroed by
+// k_ff_zero_layer).  A wavefront takes 32 pixels (two A tiles: lane i16's are 2 i16 and 2 i16 + 1,
+// 16 bytes) and 16 BT right-hand sides, G is read once for them, four steps of four sensors
+// ahead; r passes through LDS, FA_M sensors at a time, [sensor][right-hand side].  The two
+// products of each part have sums of their own (half the chain of rounding).  180 sensors, 32
+// right-hand sides, 256^2: 84 us with LDS tiles on the vector units, 44 us now; 82 with every
+// lane storing its own eight pixels (64 lines per store) instead of through LDS.
+constexpr int FA_M = 128, FA_P = 128;  // sensors per pass, pixels per block
+template <int BT>
 __global__ __launch_bounds__(256) void k_ff_adjoint(int dim, int B, int M, int ne, int w, int n, const c32* G,
                                                      const c32* r, const float* fpl, c32* s_ext, c32* rhs_ext) {
-  __shared__ c32 sg[TT][TT + 1];  // [sensor][pixel]
-  __shared__ c32 sr[TT][TT + 1];  // [rhs][sensor]
+  constexpr int BW = 16 * BT, U = 4;
+  static_assert(FA_M == FA_P, "one buffer for the sensors' values and the pixels' results");
+  __shared__ c32 buf[BW * (FA_P + 1) > FA_M * (BW + 1) ? BW * (FA_P + 1) : FA_M * (BW + 1)];
+  c32(*sr)[BW + 1] = reinterpret_cast<c32(*)[BW + 1]>(buf);
+  const int tid = threadIdx.x, lane = tid % 64, i16 = lane % 16, g = lane / 16, b0 = blockIdx.y * BW;
   const long long Ni = dim == 2 ? (long long)n * n : (long long)n * n * n;
   const long long Ne = dim == 2 ? (long long)ne * ne : (long long)ne * ne * ne;
-  const long long i0 = (long long)blockIdx.x * TT;
-  const int b0 = blockIdx.y * TT;
-  const int tx = threadIdx.x % TT, ty = threadIdx.x / TT;
-  c32 acc[4];
-  for (int q = 0; q < 4; ++q) acc[q] = make_float2(0.f, 0.f);
-  for (int mb = 0; mb < M; mb += TT) {
-    for (int q = 0; q < 4; ++q) {
-      const int row = ty + 8 * q;
-      const long long i = i0 + tx;
-      sg[row][tx] = (mb + row < M && i < Ni) ? G[(long long)(mb + row) * Ni + i] : make_float2(0.f, 0.f);
-      sr[row][tx] = (b0 + row < B && mb + tx < M) ? r[(long long)(b0 + row) * M + mb + tx] : make_float2(0.f, 0.f);
+  const long long i0 = ((long long)blockIdx.x * 4 + tid / 64) * 32;
+  // pairs past the last pixel start there (G has one entry more than its rows), and what they
+  // add to is not stored
+  const c32* gp = G + min(i0 + 2 * i16, Ni - 1);
+  f32x4 re[2][2][BT], im[2][2][BT];  // [x or y of G][pixel tile][right-hand sides]
+#pragma unroll
+  for (int h = 0; h < 2; ++h)
+#pragma unroll
+    for (int q = 0; q < 2; ++q)
+#pragma unroll
+      for (int t = 0; t < BT; ++t) re[h][q][t] = im[h][q][t] = f32x4{0.f, 0.f, 0.f, 0.f};
+  f32x4 gn[U];
+  auto fetch = [&](int m0) {  // U steps from sensor m0 (past the last sensor: the last one, r is zero there)
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      gn[u] = *reinterpret_cast<const f32x4_a8*>(gp + (long long)min(m0 + 4 * u + g, M - 1) * Ni);
+  };
+  fetch(0);
+  for (int mb = 0; mb < M; mb += FA_M) {
+    __syncthreads();
+    for (int q = tid; q < FA_M * BW; q += 256) {
+      const int m = q % FA_M, b = q / FA_M;
+      sr[m][b] = mb + m < M && b0 + b < B ? r[(long long)(b0 + b) * M + mb + m] : make_float2(0.f, 0.f);
     }
     __syncthreads();
-    // thread (tx, ty): pixel i0 + tx, RHS b0 + ty + 8 q
-    for (int t = 0; t < TT; ++t) {
-      const c32 gv = sg[t][tx];
-      for (int q = 0; q < 4; ++q) acc[q] = cadd(acc[q], cconjmul(gv, sr[ty + 8 * q][t]));
+    const int mend = min(FA_M, M - mb);
+    for (int m = 0; m < mend; m += 4 * U) {
+      f32x4 gv[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) gv[u] = gn[u];
+      if (mb + m + 4 * U < M) fetch(mb + m + 4 * U);
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        c32 rv[BT];
+#pragma unroll
+        for (int t = 0; t < BT; ++t) rv[t] = sr[m + 4 * u + g][16 * t + i16];
+#pragma unroll
+        for (int q = 0; q < 2; ++q)
+#pragma unroll
+          for (int t = 0; t < BT; ++t) {
+            re[0][q][t] = mfma4(gv[u][2 * q], rv[t].x, re[0][q][t]);
+            im[0][q][t] = mfma4(gv[u][2 * q], rv[t].y, im[0][q][t]);
+            re[1][q][t] = mfma4(gv[u][2 * q + 1], rv[t].y, re[1][q][t]);
+            im[1][q][t] = mfma4(gv[u][2 * q + 1], rv[t].x, im[1][q][t]);
+          }
+      }
     }
-    __syncthreads();
   }
-  const long long i = i0 + tx;
+  // through LDS, so that a wavefront stores 64 consecutive pixels of one right-hand side
+  c32(*out)[FA_P + 1] = reinterpret_cast<c32(*)[FA_P + 1]>(buf);
+  __syncthreads();
+#pragma unroll
+  for (int c = 0; c < 4; ++c)
+#pragma unroll
+    for (int o = 0; o < 2; ++o)
+#pragma unroll
+      for (int t = 0; t < BT; ++t)
+        out[16 * t + i16][(tid / 64) * 32 + 2 * (4 * g + c) + o] =
+            make_float2(re[0][o][t][c] + re[1][o][t][c], im[0][o][t][c] - im[1][o][t][c]);
+  __syncthreads();
+  const int px = tid % FA_P;
+  const long long i = (long long)blockIdx.x * FA_P + px;
   if (i >= Ni) return;
-  const Coord c = coord_of32((unsigned)i, (unsigned)n, dim);
-  const long long p = dim == 2 ? (long long)(c.y + w) * ne + (c.x + w)
-                               : ((long long)(c.z + w) * ne + (c.y + w)) * ne + (c.x + w);
-  for (int q = 0; q < 4; ++q) {
-    const int b = b0 + ty + 8 * q;
-    if (b < B) {
-      s_ext[(long long)b * Ne + p] = acc[q];
-      if (rhs_ext) rhs_ext[(long long)b * Ne + p] = cscale(acc[q], fpl[p]);
-    }
+  const Coord x = coord_of32((unsigned)i, (unsigned)n, dim);
+  const long long p = dim == 2 ? (long long)(x.y + w) * ne + (x.x + w)
+                               : ((long long)(x.z + w) * ne + (x.y + w)) * ne + (x.x + w);
+  const float f = rhs_ext ? fpl[p] : 0.f;
+  for (int b = tid / FA_P; b < BW && b0 + b < B; b += 256 / FA_P) {
+    const c32 v = out[b][px];
+    s_ext[(long long)(b0 + b) * Ne + p] = v;
+    if (rhs_ext) rhs_ext[(long long)(b0 + b) * Ne + p] = cscale(v, f);
   }
+}
+
+// zeros outside Omega
+__global__ void k_ff_zero_layer(int dim, int ne, int w, int n, long long Ne, c32* s_ext, c32* rhs_ext) {
+  const long long p = (long long)blockIdx.x * blockDim.x + threadIdx.x;
+  if (p >= Ne) return;
+  const Coord c = coord_of32((unsigned)p, (unsigned)ne, dim);
+  const bool in = c.x >= w && c.x < w + n && c.y >= w && c.y < w + n && (dim == 2 || (c.z >= w && c.z < w + n));
+  if (in) return;
+  const long long t = blockIdx.y * Ne + p;
+  s_ext[t] = make_float2(0.f, 0.f);
+  if (rhs_ext) rhs_ext[t] = make_float2(0.f, 0.f);
 }
 
 inline unsigned nb(long long n, int bs) { return (unsigned)((n + bs - 1) / bs); }
@@ -164,24 +297,39 @@ void launch_ff_matrix(hipStream_t s, int dim, int n, int M, const double* sens, 
 }
 
 int ff_splits(long long Ni) {
-  // pixel chunks of at least 1024 points, at most 64 chunks
-  long long k = Ni / 1024;
-  return (int)(k < 1 ? 1 : (k > 64 ? 64 : k));
+  // pixel chunks of at least 256 points, at most 256 chunks
+  const long long k = Ni / 256;
+  return (int)(k < 1 ? 1 : (k > 256 ? 256 : k));
 }
 
 void launch_ff_forward(hipStream_t s, int dim, int B, int M, int ne, int w, int n, const float* fpl, const c32* uin,
                        const c32* usc, const c32* G, c32* src, c32* part, c32* y) {
   const long long Ni = dim == 2 ? (long long)n * n : (long long)n * n * n;
   hipLaunchKernelGGL(k_ff_source, dim3(nb(Ni, 256), B), dim3(256), 0, s, dim, B, ne, w, n, fpl, uin, usc, src);
-  const int ns = ff_splits(Ni);
-  const long long chunk = (Ni + ns - 1) / ns;
-  hipLaunchKernelGGL(k_ff_apply, dim3(nb(M, TT), nb(B, TT), ns), dim3(256), 0, s, B, M, Ni, chunk, G, src, part);
-  hipLaunchKernelGGL(k_ff_reduce, dim3(nb((long long)B * M, 256)), dim3(256), 0, s, B, M, ns, part, y);
+  // chunks for two wavefronts per SIMD (2048) over the sensor tiles and right-hand side groups
+  const int bt0 = B <= 16 ? 1 : (B <= 32 ? 2 : 4);
+  const int want = std::max(1, 2048 / (int)(nb(M, 16) * nb(B, 16 * bt0)));
+  const int ns = std::min(ff_splits(Ni), want);
+  const long long chunk = ((Ni + ns - 1) / ns + 31) / 32 * 32;
+  const int used = (int)((Ni + chunk - 1) / chunk);
+  auto apply = [&](auto kernel, int bt) {
+    hipLaunchKernelGGL(kernel, dim3(nb(M, 64), used, nb(B, 16 * bt)), dim3(256), 0, s, B, M, Ni, chunk, G, src, part);
+  };
+  if (B <= 16) apply(k_ff_apply<1>, 1);
+  else if (B <= 32) apply(k_ff_apply<2>, 2);
+  else apply(k_ff_apply<4>, 4);
+  hipLaunchKernelGGL(k_ff_reduce, dim3(nb((long long)B * M, 64)), dim3(256), 0, s, B * M, used, part, y);
 }
 
 void launch_ff_adjoint(hipStream_t s, int dim, int B, int M, int ne, int w, int n, const c32* G, const c32* r,
                        const float* fpl, c32* s_ext, c32* rhs_ext) {
   const long long Ni = dim == 2 ? (long long)n * n : (long long)n * n * n;
-  hipLaunchKernelGGL(k_ff_adjoint, dim3(nb(Ni, TT), nb(B, TT)), dim3(256), 0, s, dim, B, M, ne, w, n, G, r, fpl, s_ext,
-                     rhs_ext);
+  const long long Ne = dim == 2 ? (long long)ne * ne : (long long)ne * ne * ne;
+  hipLaunchKernelGGL(k_ff_zero_layer, dim3(nb(Ne, 256), B), dim3(256), 0, s, dim, ne, w, n, Ne, s_ext, rhs_ext);
+  auto adjoint = [&](auto kernel, int bt) {
+    hipLaunchKernelGGL(kernel, dim3(nb(Ni, FA_P), nb(B, 16 * bt)), dim3(256), 0, s, dim, B, M, ne, w, n, G, r, fpl, s_ext,
+                       rhs_ext);
+  };
+  if (B <= 16) adjoint(k_ff_adjoint<1>, 1);
+  else adjoint(k_ff_adjoint<2>, 2);
 }
