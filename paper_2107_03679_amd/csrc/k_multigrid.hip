@@ -1246,83 +1246,67 @@ __global__ void k_apply(int dim, VecSet x, ScaleSet xs, LevelArgs lv, float out_
   y.p[(long long)b * y.stride + p] = cscale(out, out_scale * scale_of(xs, b));
 }
 
-// z_b = M r_b with M given transposed (minvT[k * Nc + row] = M[row][k]):
-// one thread per (row, right-hand side); r_b is staged in LDS and broadcast,
-// rows are read coalesced from the transposed inverse.
-constexpr int CS_MAX = 4096;
-__global__ __launch_bounds__(256) void k_coarse_solve(const c32* minvT, int Nc, VecSet r, VecSet z,
-                                                      const int* active) {
-  __shared__ c32 sr[CS_MAX];
-  const int b = blockIdx.y;
-  if (active && !active[b]) return;
-  const c32* rb = r.p + (long long)b * r.stride;
-  for (int k = threadIdx.x; k < Nc; k += blockDim.x) sr[k] = rb[k];
-  __syncthreads();
-  const int row = blockIdx.x * blockDim.x + threadIdx.x;
-  if (row >= Nc) return;
-  c32 acc0 = make_float2(0.f, 0.f), acc1 = acc0;
-  int k = 0;
-  for (; k + 1 < Nc; k += 2) {
-    acc0 = cfma(minvT[(long long)k * Nc + row], sr[k], acc0);
-    acc1 = cfma(minvT[(long long)(k + 1) * Nc + row], sr[k + 1], acc1);
-  }
-  if (k < Nc) acc0 = cfma(minvT[(long long)k * Nc + row], sr[k], acc0);
-  z.p[(long long)b * z.stride + row] = cadd(acc0, acc1);
-}
-
-// The same product for all right-hand sides as one complex matrix product
-// Z = M R: a block computes 64 rows x 16 right-hand sides over one of
-// CS_KSPLIT slices of the inner index (tiles of 32 staged in LDS, 2 x 2
-// outputs per thread), writing its slice's partial sums; k_coarse_reduce adds
-// the slices in a fixed order.  The inverse is read once per 16 right-hand
-// sides instead of once per right-hand side.
-constexpr int CS_KSPLIT = 8, CS_RT = 64, CS_BT = 16, CS_KC = 32;
-__global__ __launch_bounds__(256) void k_coarse_gemm(const c32* minvT, int Nc, int B, VecSet r, c32* part) {
-  __shared__ c32 sA[CS_KC][CS_RT];
-  __shared__ c32 sR[CS_KC][CS_BT];
-  const int r0 = blockIdx.x * CS_RT, b0 = blockIdx.y * CS_BT;
-  const int klen = ((Nc + CS_KSPLIT - 1) / CS_KSPLIT + CS_KC - 1) / CS_KC * CS_KC;
-  const int kb = blockIdx.z * klen, ke = min(Nc, kb + klen);
-  const int ry = threadIdx.x % 32, bx = threadIdx.x / 32;
-  c32 a00 = make_float2(0.f, 0.f), a01 = a00, a10 = a00, a11 = a00;
-  for (int k0 = kb; k0 < ke; k0 += CS_KC) {
-    for (int i = threadIdx.x; i < CS_KC * CS_RT; i += 256) {
-      const int kk = i / CS_RT, rr = i % CS_RT;
-      const bool ok = k0 + kk < ke && r0 + rr < Nc;
-      sA[kk][rr] = ok ? minvT[(long long)(k0 + kk) * Nc + r0 + rr] : make_float2(0.f, 0.f);
-    }
-    for (int i = threadIdx.x; i < CS_KC * CS_BT; i += 256) {
-      const int q = i / CS_KC, kk = i % CS_KC;
-      const bool ok = k0 + kk < ke && b0 + q < B;
-      sR[kk][q] = ok ? r.p[(long long)(b0 + q) * r.stride + k0 + kk] : make_float2(0.f, 0.f);
-    }
-    __syncthreads();
-#pragma unroll 8
-    for (int kk = 0; kk < CS_KC; ++kk) {
-      const c32 m0 = sA[kk][ry], m1 = sA[kk][ry + 32], v0 = sR[kk][bx], v1 = sR[kk][bx + 8];
-      a00 = cfma(m0, v0, a00);
-      a01 = cfma(m0, v1, a01);
-      a10 = cfma(m1, v0, a10);
-      a11 = cfma(m1, v1, a11);
-    }
-    __syncthreads();
-  }
-  c32* pp = part + (long long)blockIdx.z * B * Nc;
-  const int ra = r0 + ry, rb = r0 + ry + 32, ba = b0 + bx, bb = b0 + bx + 8;
-  if (ra < Nc && ba < B) pp[(long long)ba * Nc + ra] = a00;
-  if (ra < Nc && bb < B) pp[(long long)bb * Nc + ra] = a01;
-  if (rb < Nc && ba < B) pp[(long long)ba * Nc + rb] = a10;
-  if (rb < Nc && bb < B) pp[(long long)bb * Nc + rb] = a11;
-}
-
-__global__ __launch_bounds__(256) void k_coarse_reduce(const c32* part, int Nc, int B, VecSet z, const int* active) {
-  const int b = blockIdx.y;
-  const int row = blockIdx.x * 256 + threadIdx.x;
-  if (row >= Nc || (active && !active[b])) return;
-  c32 acc = make_float2(0.f, 0.f);
+// Z = M R, the exact coarsest solve of a batch, with M given transposed (minvT[k Nc + row] =
+// M[row][k]) and read once per BT right-hand sides.  A workgroup takes 16 rows: threads (row, column group), 64 groups, each with the entries of its columns
+// loaded straight from memory (128 bytes a column, KC columns ahead of the products) and R
+// passing through LDS, KC columns at a time; then the groups' sums are added in a fixed order.
+// No partial sums leave the workgroup.  Bound by the inverse's 8 Nc^2 bytes: 24 MB at 12^3, in
+// 21 us for 8 right-hand sides (45 + 5 with 64-row tiles, eight column slices and a second
+// launch; the same product with one thread per row, for fewer than four right-hand sides, made a
+// cycle at 100^3 x 1 208 us, now 126).
+constexpr int CS_ROWS = 16, CS_NT = 1024, CS_G = CS_NT / CS_ROWS;
+template <int BT, int CS_KC>
+__global__ __launch_bounds__(CS_NT) void k_coarse_gemm(const c32* minvT, int Nc, int B, VecSet r, VecSet z,
+                                                       const int* active) {
+  constexpr int CS_U = CS_KC / CS_G;
+  __shared__ __align__(16) c32 sR[CS_KC][BT];
+  __shared__ c32 red[CS_NT / HELM_WAVE][CS_ROWS][BT];
+  const int tid = threadIdx.x, rr = tid % CS_ROWS, g = tid / CS_ROWS, b0 = blockIdx.y * BT;
+  const int row = blockIdx.x * CS_ROWS + rr;
+  const c32* mp = minvT + min(row, Nc - 1);
+  c32 mn[CS_U];
+  auto fetch = [&](int k0) {
 #pragma unroll
-  for (int q = 0; q < CS_KSPLIT; ++q) acc = cadd(acc, part[((long long)q * B + b) * Nc + row]);
-  z.p[(long long)b * z.stride + row] = acc;
+    for (int u = 0; u < CS_U; ++u) mn[u] = mp[(long long)min(k0 + g + u * CS_G, Nc - 1) * Nc];
+  };
+  fetch(0);
+  c32 acc[BT];
+#pragma unroll
+  for (int q = 0; q < BT; ++q) acc[q] = make_float2(0.f, 0.f);
+  for (int k0 = 0; k0 < Nc; k0 += CS_KC) {
+    __syncthreads();
+    for (int i = tid; i < CS_KC * BT; i += CS_NT) {
+      const int k = i % CS_KC, q = i / CS_KC;
+      sR[k][q] = k0 + k < Nc && b0 + q < B ? r.p[(long long)(b0 + q) * r.stride + k0 + k] : make_float2(0.f, 0.f);
+    }
+    c32 m[CS_U];
+#pragma unroll
+    for (int u = 0; u < CS_U; ++u) m[u] = mn[u];
+    if (k0 + CS_KC < Nc) fetch(k0 + CS_KC);
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < CS_U; ++u)
+#pragma unroll
+      for (int q = 0; q < BT; ++q) acc[q] = cfma(m[u], sR[g + u * CS_G][q], acc[q]);  // zero past the last column
+  }
+#pragma unroll
+  for (int q = 0; q < BT; ++q) {
+#pragma unroll
+    for (int off = CS_ROWS; off < HELM_WAVE; off <<= 1) {
+      acc[q].x += __shfl_xor(acc[q].x, off, HELM_WAVE);
+      acc[q].y += __shfl_xor(acc[q].y, off, HELM_WAVE);
+    }
+    if (tid % HELM_WAVE < CS_ROWS) red[tid / HELM_WAVE][rr][q] = acc[q];
+  }
+  __syncthreads();
+  if (tid < CS_ROWS * BT) {
+    const int o = tid % CS_ROWS, q = tid / CS_ROWS, b = b0 + q, row_o = blockIdx.x * CS_ROWS + o;
+    if (row_o >= Nc || b >= B || (active && !active[b])) return;
+    c32 s = make_float2(0.f, 0.f);
+#pragma unroll
+    for (int w = 0; w < CS_NT / HELM_WAVE; ++w) s = cadd(s, red[w][o][q]);
+    z.p[(long long)b * z.stride + row_o] = s;
+  }
 }
 
 inline unsigned nblocks(long long n, int bs) { return (unsigned)((n + bs - 1) / bs); }
@@ -1524,18 +1508,16 @@ void launch_prolong_add(hipStream_t s, int dim, int B, VecSet ec, int nc, VecSet
                      N, active);
 }
 
-void launch_coarse_solve(hipStream_t s, int B, const c32* minvT, int Nc, VecSet r, VecSet z, const int* active,
-                         c32* part) {
-  if (part && B >= 4) {  // as one matrix product (part: coarse_solve_part_size(B, Nc) entries)
-    hipLaunchKernelGGL(k_coarse_gemm, dim3(nblocks(Nc, CS_RT), nblocks(B, CS_BT), CS_KSPLIT), dim3(256), 0, s, minvT,
-                       Nc, B, r, part);
-    hipLaunchKernelGGL(k_coarse_reduce, dim3(nblocks(Nc, 256), B), dim3(256), 0, s, part, Nc, B, z, active);
-    return;
-  }
-  hipLaunchKernelGGL(k_coarse_solve, dim3(nblocks(Nc, 256), B), dim3(256), 0, s, minvT, Nc, r, z, active);
+void launch_coarse_solve(hipStream_t s, int B, const c32* minvT, int Nc, VecSet r, VecSet z, const int* active) {
+  auto gemm = [&](auto kernel, int bt) {
+    hipLaunchKernelGGL(kernel, dim3(nblocks(Nc, CS_ROWS), nblocks(B, bt)), dim3(CS_NT), 0, s, minvT, Nc, B, r, z,
+                       active);
+  };
+  if (B == 1) gemm(k_coarse_gemm<1, 512>, 1);
+  else if (B <= 4) gemm(k_coarse_gemm<4, 512>, 4);
+  else if (B <= 8) gemm(k_coarse_gemm<8, 512>, 8);
+  else gemm(k_coarse_gemm<16, 256>, 16);
 }
-
-size_t coarse_solve_part_size(int B, int Nc) { return (size_t)CS_KSPLIT * B * Nc; }
 
 void launch_apply(hipStream_t s, int dim, int B, VecSet x, ScaleSet xs, LevelArgs lv, float out_scale, VecSet y,
                   const int* active) {

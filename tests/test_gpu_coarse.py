@@ -72,3 +72,20 @@ def test_coarsest_inverse_matches_oracle(n, levels, d):
     ref = np.stack([hier.coarse_lu.solve(ri.ravel()).reshape(shape) for ri in r])
     # the 64-bit inverse rounded to 32 bits and a single-precision product of a well-conditioned matrix
     assert rel(z, ref) < 1e-6
+
+
+@pytest.mark.parametrize("n, levels, B", [(161, 4, 1), (161, 4, 3), (161, 4, 8), (161, 4, 17), (49, 5, 9)])
+def test_coarse_products_agree(n, levels, B):
+    """The product's tiles of 1, 4, 8 and 16 right-hand sides (529 points: two passes over the
+    columns, the last rows' workgroup with one row; 25: one pass) against the oracle and, sums in
+    the same order, each other."""
+    nmap = medium(n, seed=8)
+    prob = oracle_problem(nmap, levels=levels)
+    hier = Hierarchy(prob)
+    shape = (hier.sizes[-1],) * 2
+    r = synth.complex_field((B, *shape), 73)
+    with gpu_context(nmap, levels=levels, max_batch=B, restart=1) as ctx:
+        z = ctx.coarse_solve(to_dev(r))
+        assert bool((ctx.coarse_solve(to_dev(r[:1])) == z[:1]).all())
+    ref = np.stack([hier.coarse_lu.solve(ri.ravel()).reshape(shape) for ri in r])
+    assert rel(to_np(z), ref) < 1e-6
