@@ -33,6 +33,15 @@ __device__ __forceinline__ bf16x8 zero8() {
   return z;
 }
 
+// The 8 BF16 channels of a network input pixel from its 4 floats (NetSrc::f32)
+__device__ __forceinline__ bf16x8 pad_input(bf16x8 raw) {
+  const f32x4 f = __builtin_bit_cast(f32x4, raw);
+  bf16x8 o = zero8();
+#pragma unroll
+  for (int v = 0; v < 4; ++v) o[v] = (bf16)f[v];
+  return o;
+}
+
 // ---------------------------------------------------------------- layer inputs
 // Address of 8 input channels [ci0, ci0 + 8) of pixel (z, y, x) of one image for the
 // convolution's halo staging (MODE 0: plain, 2: upsample + skip), with (z, y, x) clamped
@@ -543,7 +552,7 @@ __global__ __launch_bounds__(256) void k_conv2c(ConvArgs a) {
             o[e] = (bf16)(0.25f * acc);
           }
         } else {
-          o = v[i - i0][p][0];
+          o = MODE == 3 ? pad_input(v[i - i0][p][0]) : v[i - i0][p][0];
         }
         *reinterpret_cast<bf16x8*>(tile + dst0[p] + i * RPP * TW2 * PS) = (xin[p] && yin[i - i0]) ? o : zero8();
       }
@@ -660,15 +669,15 @@ __global__ __launch_bounds__(256) void k_conv2c(ConvArgs a) {
 // ---------------------------------------------------------------- conv, 2D marching form
 // k_conv2c's sums (outputs equal bit for bit) for 2D layers with plain or
 // upsample-and-skip inputs: every k-step's weights sit in registers (loaded once per
-// block), a block walks NIT tiles down one column, the next tile's halo is loaded into
+// block), a block walks `march` tiles down one column, the next tile's halo is loaded into
 // registers while the current tile is computed, and the A operands are read PD k-steps
 // ahead.  Used for the level-0 decoder layer (48 -> 16), whose halo loads k_conv2c
 // waits for: 783 -> 701 us at 60 x 577^2 with 16 tiles per block.  The first layer and
 // the output layer ran slower marching (238 -> 328 and 317 -> 323 us), and so did the
 // 96 -> 32 layer with its 27 k-steps of weights in registers at one wavefront per SIMD
 // (534 -> 710 us, against k_conv2c's weights through LDS at three blocks per CU).
-template <int CIN, int NCO, int TH, int TW, int MODE, int NIT, int PD>
-__global__ __launch_bounds__(256) void k_conv2m(ConvArgs a) {
+template <int CIN, int NCO, int TH, int TW, int MODE, int PD>
+__global__ __launch_bounds__(256) void k_conv2m(ConvArgs a, int march) {
   constexpr int PS = CIN == 8 ? 8 : CIN + 8, CG8 = CIN / 8;
   constexpr int TW2 = TW + 2, SEG = TW / 16, MT = TH * TW / 64;
   constexpr int KS = (9 * CIN + 31) / 32, KPAD = 32 * KS;
@@ -676,8 +685,8 @@ __global__ __launch_bounds__(256) void k_conv2m(ConvArgs a) {
   extern __shared__ __align__(16) bf16 tile[];
   const int tid = threadIdx.x, l = tid % 64, g = l / 16, i16 = l % 16;
   const int wave = __builtin_amdgcn_readfirstlane(tid / 64);
-  const int H = a.H, W = a.W, x0 = blockIdx.x * TW, ty0 = blockIdx.y * NIT;
-  const int ntile = min(NIT, (H + TH - 1) / TH - ty0);  // uniform
+  const int H = a.H, W = a.W, x0 = blockIdx.x * TW, ty0 = blockIdx.y * march;
+  const int ntile = min(march, (H + TH - 1) / TH - ty0);  // uniform
   const long long img = blockIdx.z;
   const NetSrc& sr = a.src;
   const bf16* in_img = sr.in + img * ((long long)H * W * sr.in_ct) + sr.in_off;
@@ -831,7 +840,7 @@ __global__ __launch_bounds__(256) void k_conv2m(ConvArgs a) {
 // 3D layers (plain, pooled or upsample-and-skip inputs), CIN fixed at compile time: the
 // products and sums of k_conv_lds (whose marching form these follow) in the same order,
 // so the outputs are equal bit for bit, with the index arithmetic at compile time as in
-// k_conv2c.  A block computes ZM output planes of a TH x TW tile; four plane slots hold
+// k_conv2c.  A block computes `march` output planes of a TH x TW tile; four plane slots hold
 // the halo planes z - 1, z, z + 1 and the prefetched z + 2.  A k-step's lane group reads
 // tap (dz, dy, dx), channel ci: its LDS offset is the (uniform, per output plane) base of
 // slot (z - z0 + dz) mod 4 plus a compile-time constant.  The weights of every k-step
@@ -846,8 +855,8 @@ __host__ __device__ constexpr int conv3_off(int s, int g) {  // in-plane offset 
   return ((tp / 3) * TW2 + tp % 3) * PS + k % CIN;
 }
 
-template <int CIN, int NCO, int TH, int TW, int MODE, int ZM, int PD>
-__global__ __launch_bounds__(256) void k_conv3c(ConvArgs a) {
+template <int CIN, int NCO, int TH, int TW, int MODE, int PD>
+__global__ __launch_bounds__(256) void k_conv3c(ConvArgs a, int march) {
   constexpr int PS = CIN == 8 ? 8 : CIN + 8, CG8 = CIN / 8;
   constexpr int TW2 = TW + 2, SEG = TW / 16, MT = TH * TW / 64, PLANE = (TH + 2) * TW2, SLOT = PLANE * PS;
   constexpr int KS = (27 * CIN + 31) / 32, KPAD = 32 * KS;
@@ -856,9 +865,9 @@ __global__ __launch_bounds__(256) void k_conv3c(ConvArgs a) {
   const int tid = threadIdx.x, l = tid % 64, g = l / 16, i16 = l % 16;
   const int wave = __builtin_amdgcn_readfirstlane(tid / 64);
   const int D = a.D, H = a.H, W = a.W, x0 = blockIdx.x * TW, y0 = blockIdx.y * TH;
-  const int nzb = (D + ZM - 1) / ZM;
+  const int nzb = (D + march - 1) / march;
   const long long img = blockIdx.z / nzb;
-  const int z0 = (int)(blockIdx.z % nzb) * ZM, zend = min(D, z0 + ZM);
+  const int z0 = (int)(blockIdx.z % nzb) * march, zend = min(D, z0 + march);
   const NetSrc& sr = a.src;
   // MODE 1: the 2 x 2 x 2 average (zero padding) of the source at Ds x Hs x Ws
   const bf16* in_img = sr.in + img * ((long long)(MODE == 1 ? (long long)sr.Ds * sr.Hs * sr.Ws : (long long)D * H * W) * sr.in_ct) + sr.in_off;
@@ -961,7 +970,7 @@ __global__ __launch_bounds__(256) void k_conv3c(ConvArgs a) {
             o[e] = (bf16)(0.125f * acc);
           }
         } else {
-          o = v[i][p][0];
+          o = MODE == 3 ? pad_input(v[i][p][0]) : v[i][p][0];
         }
         *reinterpret_cast<bf16x8*>(tile + slot * SLOT + dst0[p] + i * RPP * TW2 * PS) =
             (xin[p] && (fl[i] & 1)) ? o : zero8();
@@ -1490,13 +1499,16 @@ void conv2c(hipStream_t s, const ConvArgs& a) {
   hipLaunchKernelGGL((k_conv2c<CIN, NCO, TH, TW, MODE, WL>), grid, dim3(256), lds, s, a);
 }
 
-template <int CIN, int NCO, int TH, int MODE, int NIT, int PD>
+template <int CIN, int NCO, int TH, int MODE, int PD>
 void conv2m(hipStream_t s, const ConvArgs& a) {
   constexpr int TW = 32;
   const size_t lds = (size_t)(TH + 2) * (TW + 2) * (CIN == 8 ? 8 : CIN + 8) * sizeof(bf16);
-  const int ty = (a.H + TH - 1) / TH;
-  const dim3 grid((a.W + TW - 1) / TW, (ty + NIT - 1) / NIT, a.nimg);
-  hipLaunchKernelGGL((k_conv2m<CIN, NCO, TH, TW, MODE, NIT, PD>), grid, dim3(256), lds, s, a);
+  const int tx = (a.W + TW - 1) / TW, ty = (a.H + TH - 1) / TH;
+  // 16 tiles a block where that leaves 1024 blocks (a march serialises its tiles: at 4 x 256^2,
+  // 64 blocks of 16 took 46 us)
+  const int march = march_planes((long long)tx * a.nimg, ty, 16, 1);
+  hipLaunchKernelGGL((k_conv2m<CIN, NCO, TH, TW, MODE, PD>), dim3(tx, (ty + march - 1) / march, a.nimg), dim3(256), lds,
+                     s, a, march);
 }
 
 // The channel-specialised kernels of the 2D network's forward layers (their tile shapes
@@ -1506,14 +1518,15 @@ void conv2m(hipStream_t s, const ConvArgs& a) {
 // slower (272-288 against 247 us at 60 x 577^2).
 bool conv2c_dispatch(hipStream_t s, const ConvArgs& a, int nco) {
   if (a.kpad != (9 * a.cin + 31) / 32 * 32) return false;
-  const int mode = a.src.pool ? 1 : (a.src.cup > 0 ? 2 : 0);
+  const int mode = a.src.f32 ? 3 : (a.src.pool ? 1 : (a.src.cup > 0 ? 2 : 0));
   switch ((a.cin << 8) | (nco << 4) | mode) {
     case (8 << 8) | (1 << 4) | 0: conv2c<8, 1, 8, 0>(s, a); return true;       // A0
+    case (8 << 8) | (1 << 4) | 3: conv2c<8, 1, 8, 3>(s, a); return true;       // A0, FP32 input
     case (32 << 8) | (4 << 4) | 1: conv2c<32, 4, 8, 1>(s, a); return true;     // A2
     case (64 << 8) | (4 << 4) | 1: conv2c<64, 4, 8, 1>(s, a); return true;     // A3
     case (128 << 8) | (4 << 4) | 2: conv2c<128, 4, 4, 2>(s, a); return true;   // B2
     case (96 << 8) | (2 << 4) | 2: conv2c<96, 2, 4, 2>(s, a); return true;     // B1
-    case (48 << 8) | (1 << 4) | 2: conv2m<48, 1, 8, 2, 16, 1>(s, a); return true;     // B0 (marching)
+    case (48 << 8) | (1 << 4) | 2: conv2m<48, 1, 8, 2, 1>(s, a); return true;     // B0 (marching)
     case (16 << 8) | (1 << 4) | 0: conv2c<16, 1, 8, 0>(s, a); return true;     // O
     default: return false;
   }
@@ -1521,10 +1534,15 @@ bool conv2c_dispatch(hipStream_t s, const ConvArgs& a, int nco) {
 
 template <int CIN, int MODE, int PD = 1, int NCO = 1>
 void conv3c(hipStream_t s, const ConvArgs& a) {
-  constexpr int TH = 4, TW = 32, ZM = 8;
+  constexpr int TH = 4, TW = 32;
   const size_t lds = (size_t)4 * (TH + 2) * (TW + 2) * (CIN == 8 ? 8 : CIN + 8) * sizeof(bf16);
-  const dim3 grid((a.W + TW - 1) / TW, (a.H + TH - 1) / TH, a.nimg * ((a.D + ZM - 1) / ZM));
-  hipLaunchKernelGGL((k_conv3c<CIN, NCO, TH, TW, MODE, ZM, PD>), grid, dim3(256), lds, s, a);
+  const int tx = (a.W + TW - 1) / TW, ty = (a.H + TH - 1) / TH;
+  // 8 planes a block where that leaves one block per CU: a block starts with three planes and its
+  // weights, so more blocks than CUs cost as much as they hide (2 x 120^3: 526 us for targets of
+  // 128 and 256 blocks, 541 for 512, 580 for 1024; 2 x 40^3: 128, 119, 122, 130)
+  const int march = march_planes((long long)tx * ty * a.nimg, a.D, 8, 1, 256);
+  const dim3 grid(tx, ty, a.nimg * ((a.D + march - 1) / march));
+  hipLaunchKernelGGL((k_conv3c<CIN, NCO, TH, TW, MODE, PD>), grid, dim3(256), lds, s, a, march);
 }
 
 // The channel-specialised kernels of the 3D network's layers (the generic marching
@@ -1534,7 +1552,7 @@ void conv3c(hipStream_t s, const ConvArgs& a) {
 // ahead.  False when the layer has none (A3 and B2: weights of 55 and 110 KB).
 bool conv3c_dispatch(hipStream_t s, const ConvArgs& a, int nco) {
   if (a.kpad != (27 * a.cin + 31) / 32 * 32) return false;
-  const int mode = a.src.pool ? 1 : (a.src.cup > 0 ? 2 : 0);
+  const int mode = a.src.f32 ? 3 : (a.src.pool ? 1 : (a.src.cup > 0 ? 2 : 0));
   if (nco == 2) {
     if (a.cin == 16 && mode == 1) {
       conv3c<16, 1, 1, 2>(s, a);  // A2 (pooled input, two output tiles)
@@ -1546,6 +1564,7 @@ bool conv3c_dispatch(hipStream_t s, const ConvArgs& a, int nco) {
   switch ((a.cin << 4) | mode) {
     case (16 << 4) | 1: conv3c<16, 1>(s, a); return true;  // A1 (pooled input)
     case (8 << 4) | 0: conv3c<8, 0>(s, a); return true;    // A0
+    case (8 << 4) | 3: conv3c<8, 3>(s, a); return true;    // A0, FP32 input
     case (32 << 4) | 2: conv3c<32, 2>(s, a); return true;  // B0
     case (48 << 4) | 2: conv3c<48, 2, 3>(s, a); return true;  // B1
     case (16 << 4) | 0: conv3c<16, 0>(s, a); return true;  // O

@@ -21,6 +21,8 @@ struct NetSrc {
   int up_ct, cup;
   int pool, Hs, Ws;
   int Ds;
+  int f32;  // 1: `in` is the network's input as the caller has it, 4 floats per pixel at 16-byte
+            // alignment (as wide as the 8 BF16 channels they become), not with the generic kernels
 };
 
 struct ConvArgs {
