@@ -15,41 +15,90 @@ namespace {
 
 constexpr int CC_NT = 1024;
 
+// The three stencils below read their neighbours without branches, from the nearest point of
+// the grid, and select: a read under `inside` is a branch and a wait of its own for each
+// neighbour, and a stage of these kernels is little else.
+
+// sum of the in-grid neighbours of point p (the order of neighbour_sum)
+template <int DIM>
+__device__ __forceinline__ c32 neighbours(const c32* v, int p, const Coord& c, int n) {
+  const int st[3] = {1, n, n * n}, x[3] = {c.x, c.y, c.z};
+  c32 q[2 * DIM];
+#pragma unroll
+  for (int d = 0; d < DIM; ++d) {
+    q[2 * d] = v[x[d] > 0 ? p - st[d] : p];
+    q[2 * d + 1] = v[x[d] < n - 1 ? p + st[d] : p];
+  }
+  c32 s = make_float2(0.f, 0.f);
+#pragma unroll
+  for (int d = 0; d < DIM; ++d) {
+    const bool lo = x[d] > 0, hi = x[d] < n - 1;
+    s.x += lo ? q[2 * d].x : 0.f;
+    s.y += lo ? q[2 * d].y : 0.f;
+    s.x += hi ? q[2 * d + 1].x : 0.f;
+    s.y += hi ? q[2 * d + 1].y : 0.f;
+  }
+  return s;
+}
+
 // 4 * full weighting of s at coarse point C (neighbours outside the fine grid count as 0)
-__device__ __forceinline__ c32 fw4(const c32* s, const Coord& C, int nf, int dim) {
+template <int DIM>
+__device__ __forceinline__ c32 fw4(const c32* s, const Coord& C, int nf) {
   const float w1[3] = {0.25f, 0.5f, 0.25f};
+  int ix[3], iy[3], iz[3];
+  bool bx[3], by[3], bz[3];
+#pragma unroll
+  for (int d = 0; d < 3; ++d) {
+    const int fx = 2 * C.x + d - 1, fy = 2 * C.y + d - 1, fz = 2 * C.z + d - 1;
+    bx[d] = fx >= 0 && fx < nf;
+    by[d] = fy >= 0 && fy < nf;
+    bz[d] = fz >= 0 && fz < nf;
+    ix[d] = min(max(fx, 0), nf - 1);
+    iy[d] = min(max(fy, 0), nf - 1) * nf;
+    iz[d] = min(max(fz, 0), nf - 1) * nf * nf;
+  }
   c32 acc = make_float2(0.f, 0.f);
-  const int zr = dim == 3 ? 1 : 0;
-  for (int dz = -zr; dz <= zr; ++dz)
-    for (int dy = -1; dy <= 1; ++dy)
-      for (int dx = -1; dx <= 1; ++dx) {
-        const int fx = 2 * C.x + dx, fy = 2 * C.y + dy, fz = dim == 3 ? 2 * C.z + dz : 0;
-        if (fx < 0 || fx >= nf || fy < 0 || fy >= nf || fz < 0 || fz >= nf) continue;
-        const float wgt = w1[dx + 1] * w1[dy + 1] * (dim == 3 ? w1[dz + 1] : 1.0f);
-        acc = cadd(acc, cscale(s[((long long)fz * nf + fy) * nf + fx], wgt));
-      }
+#pragma unroll
+  for (int dz = DIM == 3 ? 0 : 1; dz <= (DIM == 3 ? 2 : 1); ++dz) {
+    c32 v[9];
+#pragma unroll
+    for (int k = 0; k < 9; ++k) v[k] = s[(DIM == 3 ? iz[dz] : 0) + iy[k / 3] + ix[k % 3]];
+#pragma unroll
+    for (int k = 0; k < 9; ++k) {
+      const bool in = bx[k % 3] && by[k / 3] && (DIM == 2 || bz[dz]);
+      const float wgt = w1[k % 3] * w1[k / 3] * (DIM == 3 ? w1[dz] : 1.0f);
+      acc.x = fmaf(in ? v[k].x : 0.f, wgt, acc.x);
+      acc.y = fmaf(in ? v[k].y : 0.f, wgt, acc.y);
+    }
+  }
   return cscale(acc, 4.0f);
 }
 
 // (P e)(f): bilinear / trilinear prolongation from the coarse grid (nc points per side)
-__device__ __forceinline__ c32 prolong_at(const c32* e, const Coord& f, int nc, int dim) {
+template <int DIM>
+__device__ __forceinline__ c32 prolong_at(const c32* e, const Coord& f, int nc) {
+  const int ox = f.x & 1, oy = f.y & 1, oz = DIM == 3 ? f.z & 1 : 0;
+  const float wx = ox ? 0.5f : 1.f, wy = oy ? 0.5f : 1.f, wz = oz ? 0.5f : 1.f, w = wx * wy * wz;
+  const int base = ((DIM == 3 ? (f.z >> 1) * nc : 0) + (f.y >> 1)) * nc + (f.x >> 1);
+  c32 v[1 << DIM];
+#pragma unroll
+  for (int k = 0; k < (1 << DIM); ++k)
+    v[k] = e[base + (k & 1) * ox + (k >> 1 & 1) * oy * nc + (DIM == 3 ? (k >> 2) * oz * nc * nc : 0)];
   c32 acc = make_float2(0.f, 0.f);
-  const int oz = dim == 3 ? (f.z & 1) : 0;
-  for (int kz = 0; kz <= oz; ++kz)
-    for (int ky = 0; ky <= (f.y & 1); ++ky)
-      for (int kx = 0; kx <= (f.x & 1); ++kx) {
-        const int I = (f.x >> 1) + kx, J = (f.y >> 1) + ky, K = dim == 3 ? (f.z >> 1) + kz : 0;
-        const float wgt = ((f.x & 1) ? 0.5f : 1.0f) * ((f.y & 1) ? 0.5f : 1.0f) * (oz ? 0.5f : 1.0f);
-        acc = cadd(acc, cscale(e[((long long)K * nc + J) * nc + I], wgt));
-      }
+#pragma unroll
+  for (int k = 0; k < (1 << DIM); ++k) {  // a second point along an even axis counts 0
+    const bool in = (!(k & 1) || ox) && (!(k >> 1 & 1) || oy) && (!(k >> 2) || oz);
+    acc.x = fmaf(in ? v[k].x : 0.f, w, acc.x);
+    acc.y = fmaf(in ? v[k].y : 0.f, w, acc.y);
+  }
   return acc;
 }
 
+template <int DIM>
 __global__ __launch_bounds__(CC_NT) void k_coarse_cycle(CoarseCycleArgs a) {
   __shared__ c32 red[CC_NT];
   const int b = blockIdx.x;
   if (a.active && !a.active[b]) return;
-  const int dim = a.dim;
   const float om = a.omega;
   // ---- down ----
   for (int l = a.lp; l < a.L - 1; ++l) {
@@ -61,14 +110,14 @@ __global__ __launch_bounds__(CC_NT) void k_coarse_cycle(CoarseCycleArgs a) {
     for (int p = threadIdx.x; p < F.N; p += CC_NT) e[p] = cmul(F.wd[p], r[p]);
     __syncthreads();
     for (int p = threadIdx.x; p < F.N; p += CC_NT) {
-      const Coord c = coord_of32((unsigned)p, (unsigned)F.n, dim);
-      t[p] = cadd(cscale(r[p], 1.0f - om), neighbour_sum(e, p, c, F.n, dim));
+      const Coord c = coord_of32((unsigned)p, (unsigned)F.n, DIM);
+      t[p] = cadd(cscale(r[p], 1.0f - om), neighbours<DIM>(e, p, c, F.n));
     }
     __syncthreads();
     c32* rcn = C.rc + (long long)b * C.N;
     for (int q = threadIdx.x; q < C.N; q += CC_NT) {
-      const Coord cq = coord_of32((unsigned)q, (unsigned)C.n, dim);
-      rcn[q] = fw4(t, cq, F.n, dim);
+      const Coord cq = coord_of32((unsigned)q, (unsigned)C.n, DIM);
+      rcn[q] = fw4<DIM>(t, cq, F.n);
     }
     __syncthreads();
   }
@@ -105,13 +154,13 @@ __global__ __launch_bounds__(CC_NT) void k_coarse_cycle(CoarseCycleArgs a) {
     c32* t = F.t + (long long)b * F.N;
     const c32* ec = C.e + (long long)b * C.N;
     for (int p = threadIdx.x; p < F.N; p += CC_NT) {
-      const Coord c = coord_of32((unsigned)p, (unsigned)F.n, dim);
-      t[p] = cadd(e[p], prolong_at(ec, c, C.n, dim));
+      const Coord c = coord_of32((unsigned)p, (unsigned)F.n, DIM);
+      t[p] = cadd(e[p], prolong_at<DIM>(ec, c, C.n));
     }
     __syncthreads();
     for (int p = threadIdx.x; p < F.N; p += CC_NT) {
-      const Coord c = coord_of32((unsigned)p, (unsigned)F.n, dim);
-      e[p] = cadd(cscale(t[p], 1.0f - om), cmul(F.wd[p], cadd(r[p], neighbour_sum(t, p, c, F.n, dim))));
+      const Coord c = coord_of32((unsigned)p, (unsigned)F.n, DIM);
+      e[p] = cadd(cscale(t[p], 1.0f - om), cmul(F.wd[p], cadd(r[p], neighbours<DIM>(t, p, c, F.n))));
     }
     __syncthreads();
   }
@@ -132,11 +181,11 @@ __device__ __forceinline__ int lds_base(const CoarseCycleArgs& a, int l) {
   return o;
 }
 
+template <int DIM>
 __global__ __launch_bounds__(CC_NT) void k_coarse_cycle_lds(CoarseCycleArgs a) {
   extern __shared__ c32 lds[];
   const int b = blockIdx.x;
   if (a.active && !a.active[b]) return;
-  const int dim = a.dim;
   const float om = a.omega;
   auto R = [&](int l) { return lds + lds_base(a, l); };
   auto E = [&](int l) { return lds + lds_base(a, l) + (int)a.lv[l].N; };
@@ -173,13 +222,13 @@ __global__ __launch_bounds__(CC_NT) void k_coarse_cycle_lds(CoarseCycleArgs a) {
     for (int p = threadIdx.x; p < Nf; p += CC_NT) e[p] = cmul(F.wd[p], r[p]);
     __syncthreads();
     for (int p = threadIdx.x; p < Nf; p += CC_NT) {
-      const Coord c = coord_of32((unsigned)p, (unsigned)F.n, dim);
-      t[p] = cadd(cscale(r[p], 1.0f - om), neighbour_sum(e, p, c, F.n, dim));
+      const Coord c = coord_of32((unsigned)p, (unsigned)F.n, DIM);
+      t[p] = cadd(cscale(r[p], 1.0f - om), neighbours<DIM>(e, p, c, F.n));
     }
     __syncthreads();
     for (int q = threadIdx.x; q < Ncl; q += CC_NT) {
-      const Coord cq = coord_of32((unsigned)q, (unsigned)C.n, dim);
-      R(l + 1)[q] = fw4(t, cq, F.n, dim);
+      const Coord cq = coord_of32((unsigned)q, (unsigned)C.n, DIM);
+      R(l + 1)[q] = fw4<DIM>(t, cq, F.n);
     }
     __syncthreads();
   }
@@ -226,20 +275,20 @@ __global__ __launch_bounds__(CC_NT) void k_coarse_cycle_lds(CoarseCycleArgs a) {
     c32 *r = R(l), *e = E(l), *t = T(l);
     const c32* ec = E(l + 1);
     for (int p = threadIdx.x; p < Nf; p += CC_NT) {
-      const Coord c = coord_of32((unsigned)p, (unsigned)F.n, dim);
-      t[p] = cadd(e[p], prolong_at(ec, c, C.n, dim));
+      const Coord c = coord_of32((unsigned)p, (unsigned)F.n, DIM);
+      t[p] = cadd(e[p], prolong_at<DIM>(ec, c, C.n));
     }
     __syncthreads();
     if (l == a.lp) {
       c32* eg = F.e + (long long)b * F.N;
       for (int p = threadIdx.x; p < Nf; p += CC_NT) {
-        const Coord c = coord_of32((unsigned)p, (unsigned)F.n, dim);
-        eg[p] = cadd(cscale(t[p], 1.0f - om), cmul(F.wd[p], cadd(r[p], neighbour_sum(t, p, c, F.n, dim))));
+        const Coord c = coord_of32((unsigned)p, (unsigned)F.n, DIM);
+        eg[p] = cadd(cscale(t[p], 1.0f - om), cmul(F.wd[p], cadd(r[p], neighbours<DIM>(t, p, c, F.n))));
       }
     } else {
       for (int p = threadIdx.x; p < Nf; p += CC_NT) {
-        const Coord c = coord_of32((unsigned)p, (unsigned)F.n, dim);
-        e[p] = cadd(cscale(t[p], 1.0f - om), cmul(F.wd[p], cadd(r[p], neighbour_sum(t, p, c, F.n, dim))));
+        const Coord c = coord_of32((unsigned)p, (unsigned)F.n, DIM);
+        e[p] = cadd(cscale(t[p], 1.0f - om), cmul(F.wd[p], cadd(r[p], neighbours<DIM>(t, p, c, F.n))));
       }
       __syncthreads();
     }
@@ -308,7 +357,7 @@ __global__ __launch_bounds__(CC_NT) void k_coarse_down_rows(CoarseCycleArgs a) {
 #pragma unroll
     for (int i = 0; i < CD_MP; ++i) {
       const int p = tid + i * CC_NT;
-      if (p < Nf) st[p] = cadd(cscale(r[i], 1.0f - om), neighbour_sum(se, p, coord_of32((unsigned)p, (unsigned)n, DIM), n, DIM));
+      if (p < Nf) st[p] = cadd(cscale(r[i], 1.0f - om), neighbours<DIM>(se, p, coord_of32((unsigned)p, (unsigned)n, DIM), n));
     }
     __syncthreads();
     c32* rcg = C.rc + (long long)b * C.N;
@@ -316,7 +365,7 @@ __global__ __launch_bounds__(CC_NT) void k_coarse_down_rows(CoarseCycleArgs a) {
     for (int i = 0; i < CD_MP; ++i) {
       const int q = tid + i * CC_NT;
       if (q < Nn) {
-        r[i] = fw4(st, coord_of32((unsigned)q, (unsigned)C.n, DIM), n, DIM);
+        r[i] = fw4<DIM>(st, coord_of32((unsigned)q, (unsigned)C.n, DIM), n);
         if (last) se[q] = r[i];
         else if (blockIdx.x == 0) rcg[q] = r[i];  // the up part's
       }
@@ -380,7 +429,7 @@ __global__ __launch_bounds__(CC_NT) void k_coarse_up_rows(CoarseCycleArgs a) {
     for (int i = 0; i < CD_MP; ++i) {
       const int p = tid + i * CC_NT;
       if (p < Nf) {
-        tv[i] = cadd(cmul(w[i], r[i]), prolong_at(se, coord_of32((unsigned)p, (unsigned)n, DIM), nc, DIM));
+        tv[i] = cadd(cmul(w[i], r[i]), prolong_at<DIM>(se, coord_of32((unsigned)p, (unsigned)n, DIM), nc));
         st[p] = tv[i];
       }
     }
@@ -390,7 +439,7 @@ __global__ __launch_bounds__(CC_NT) void k_coarse_up_rows(CoarseCycleArgs a) {
     for (int i = 0; i < CD_MP; ++i) {
       const int p = tid + i * CC_NT;
       if (p < Nf) {
-        const c32 nb = neighbour_sum(st, p, coord_of32((unsigned)p, (unsigned)n, DIM), n, DIM);
+        const c32 nb = neighbours<DIM>(st, p, coord_of32((unsigned)p, (unsigned)n, DIM), n);
         const c32 v = cadd(cscale(tv[i], 1.0f - om), cmul(w[i], cadd(r[i], nb)));
         if (l == a.lp) eg[p] = v;
         else se[p] = v;
@@ -451,8 +500,12 @@ void launch_coarse_cycle(hipStream_t s, int B, const CoarseCycleArgs& a) {
     return;
   }
   const size_t lds = coarse_cycle_lds_bytes(a);
-  if (lds <= kCoarseCycleMaxLds)
-    hipLaunchKernelGGL(k_coarse_cycle_lds, dim3(B), dim3(CC_NT), lds, s, a);
-  else
-    hipLaunchKernelGGL(k_coarse_cycle, dim3(B), dim3(CC_NT), 0, s, a);
+  const bool in_lds = lds <= kCoarseCycleMaxLds;
+  if (a.dim == 2) {
+    if (in_lds) hipLaunchKernelGGL(k_coarse_cycle_lds<2>, dim3(B), dim3(CC_NT), lds, s, a);
+    else hipLaunchKernelGGL(k_coarse_cycle<2>, dim3(B), dim3(CC_NT), 0, s, a);
+  } else {
+    if (in_lds) hipLaunchKernelGGL(k_coarse_cycle_lds<3>, dim3(B), dim3(CC_NT), lds, s, a);
+    else hipLaunchKernelGGL(k_coarse_cycle<3>, dim3(B), dim3(CC_NT), 0, s, a);
+  }
 }
