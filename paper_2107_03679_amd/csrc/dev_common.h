@@ -160,6 +160,14 @@ __device__ __forceinline__ double wave_sum_d(double v) {
   return v;
 }
 
+// The value of the lane below / above in the wavefront (0 for lane 0 / 63), as a DPP shift.
+__device__ __forceinline__ float lane_below(float v) {
+  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x138, 0xf, 0xf, true));
+}
+__device__ __forceinline__ float lane_above(float v) {
+  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x130, 0xf, 0xf, true));
+}
+
 // -------------------------------------------------------------- geometry
 // Number of Sommerfeld ghost neighbours of point (x, y[, z]) on an n^d grid.
 __host__ __device__ __forceinline__ int ghosts2(int x, int y, int n) {

@@ -11,6 +11,7 @@
 // D = diag(K) includes the Sommerfeld ghost terms: D = 2d - coef - g * #ghosts.
 #include "dev_common.h"
 #include "kernels.h"
+#include "march3.h"
 
 namespace {
 
@@ -765,266 +766,264 @@ __global__ __launch_bounds__(256) void k_step_col(int nrhs, VecSet r, ScaleSet r
 }
 
 // ------------------------------------------------------------ fused 3D legs
-// The down-leg marching in z with a fixed thread map: 30 x 8 coarse points,
-// fine region 63 x 19 (2 c0 - 2 origin); each lane owns one region column and
-// every fourth row, keeping v1 of the planes f - 2 .. f and r of the plane it
-// forms s on in registers (the next plane's loads in flight); only in-plane
-// neighbours go through LDS.  Per fine plane f (bottom to top): v1(f) = W r;
-// then s(f - 1) = r - K v1 on the region's interior; then the plane's in-plane
-// full weighting is added to the coarse plane(s) it belongs to (weight 1/2 for
-// f - 1 = 2K, 1/4 to K - 1 and K for f - 1 = 2K - 1), accumulated in
-// registers; a coarse plane is written once complete.
-constexpr int DCX = 30, DCY = 8, DRX = 2 * DCX + 3, DRY = 2 * DCY + 3, DIV = (DRY + 3) / 4;
-__global__ __launch_bounds__(256) void k_down_march3c(int nrhs, VecSet r, ScaleSet rs, LevelArgs lv, float omega,
-                                                      VecSet rc, int nc, const int* active, int planes) {
-  __shared__ c32 sV[2][4 * DIV][64];
-  __shared__ c32 sS[4 * DIV][64];
+// The down-leg: DCX x CY coarse points, a fine region of 63 x (R NW) from 2 c0 - 2.  Per fine
+// plane f (bottom to top): v1(f) = W r; then s(f - 1) = r - K v1 on the region's interior,
+// weighted in z in registers (1/2 for f - 1 = 2K, 1/4 to K - 1 and K for f - 1 = 2K - 1); only a
+// finished coarse plane's sum goes through LDS for the in-plane full weighting, one plane
+// later, behind that plane's barrier.
+constexpr int DCX = 30;
+template <int R, int NW>
+__global__ __launch_bounds__(64 * NW) void k_down_march3(int nrhs, VecSet r, ScaleSet rs, LevelArgs lv, float omega,
+                                                         VecSet rc, int nc, const int* active, int planes) {
+  constexpr int CY = (R * NW - 3) / 2, CIT = (DCX * CY + 64 * NW - 1) / (64 * NW);
+  __shared__ MarchLds<R, NW> sV;
+  __shared__ c32 sS[R * NW][64];
   const int n = lv.n;
-  const int tx_n = (nc + DCX - 1) / DCX, ty_n = (nc + DCY - 1) / DCY;
+  const int tx_n = (nc + DCX - 1) / DCX, ty_n = (nc + CY - 1) / CY;
   const unsigned tiles = (unsigned)(tx_n * ty_n * ((nc + planes - 1) / planes));
   const TileId id = xcd_tile(blockIdx.x, nrhs, tiles, HELM_RHS_GROUP);
   const int b = id.b;
   if (active && !active[b]) return;
-  const int cx0 = (id.t % tx_n) * DCX, cy0 = ((id.t / tx_n) % ty_n) * DCY, kz0 = (id.t / (tx_n * ty_n)) * planes;
+  const int cx0 = (id.t % tx_n) * DCX, cy0 = ((id.t / tx_n) % ty_n) * CY, kz0 = (id.t / (tx_n * ty_n)) * planes;
   const int kz1 = min(nc, kz0 + planes);
-  const int fx0 = 2 * cx0 - 2, fy0 = 2 * cy0 - 2;
-  const float sc = scale_of(rs, b);
+  const float sc = scale_of(rs, b), om1 = 1.0f - omega;
   const c32* rb = r.p + (long long)b * r.stride;
-  const long long n2 = (long long)n * n;
-  const int lx = threadIdx.x & 63, r0 = threadIdx.x >> 6;
-  const int gx = fx0 + lx;
-  const bool inx = lx < DRX && gx >= 0 && gx < n;
-  bool in[DIV];
-  long long off[DIV];
+  c32* cb = rc.p + (long long)b * rc.stride + (long long)cy0 * nc + cx0;
+  const long long n2 = (long long)n * n, nc2 = (long long)nc * nc;
+  const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int gx = 2 * cx0 - 2 + lane, gy0 = 2 * cy0 - 2 + w * R;
+  const bool inx = gx >= 0 && gx < n;
+  const unsigned xo = inx ? (unsigned)gx * (unsigned)sizeof(c32) : 0u;
+  bool in[R];
+  int row[R];
 #pragma unroll
-  for (int it = 0; it < DIV; ++it) {
-    const int ly = r0 + 4 * it, gy = fy0 + ly;
-    in[it] = inx && ly < DRY && gy >= 0 && gy < n;
-    off[it] = in[it] ? (long long)gy * n + gx : 0;
+  for (int i = 0; i < R; ++i) {
+    in[i] = gy0 + i >= 0 && gy0 + i < n;
+    row[i] = min(max(gy0 + i, 0), n - 1) * n;
   }
-  c32 rn[DIV], wn[DIV];
-  auto fetch = [&](int f) {
-    const bool inz = f >= 0 && f < n;
+  // the coarse points this thread weights
+  unsigned coff[CIT];
+  int cl[CIT];
+  bool cin[CIT];
 #pragma unroll
-    for (int it = 0; it < DIV; ++it) {
-      const bool ok = inz && in[it];
-      const long long p = ok ? f * n2 + off[it] : 0;
-      rn[it] = ok ? rb[p] : make_float2(0.f, 0.f);
-      wn[it] = ok ? lv.wd[p] : make_float2(0.f, 0.f);
+  for (int it = 0; it < CIT; ++it) {
+    const int q = threadIdx.x + it * 64 * NW, tx = q % DCX, ty = q / DCX;
+    cin[it] = ty < CY && cx0 + tx < nc && cy0 + ty < nc;
+    coff[it] = cin[it] ? (unsigned)(ty * nc + tx) : 0u;
+    cl[it] = cin[it] ? (2 * ty + 2) * 64 + 2 * tx + 2 : 65;
+  }
+  auto weight = [&](int K) {  // coarse plane K from the sums in LDS
+#pragma unroll
+    for (int it = 0; it < CIT; ++it) {
+      const c32* p = &sS[0][0] + cl[it];
+      const c32 e = cadd(cadd(p[-1], p[1]), cadd(p[-64], p[64]));
+      const c32 d = cadd(cadd(p[-65], p[-63]), cadd(p[63], p[65]));
+      const c32 t = cadd(cadd(p[0], cscale(e, 0.5f)), cscale(d, 0.25f));
+      if (cin[it]) cb[K * nc2 + coff[it]] = t;
     }
   };
   const int f0 = 2 * kz0 - 2, f1 = 2 * kz1;  // fine planes whose v1 is needed
+  c32 rn[R], wn[R], vp[R], a[R], zs[R];
+  auto fetch = [&](int f) {
+    const long long z = (long long)min(max(f, 0), n - 1) * n2;
+    const unsigned x = here(xo);
+#pragma unroll
+    for (int i = 0; i < R; ++i) {
+      rn[i] = at_byte(rb + z + row[i], x);
+      wn[i] = at_byte(lv.wd + z + row[i], x);
+    }
+  };
   fetch(f0);
-  const int tx = threadIdx.x % DCX, ty = threadIdx.x / DCX;
-  const bool coarse = threadIdx.x < DCX * DCY && cx0 + tx < nc && cy0 + ty < nc;
-  c32 acc = make_float2(0.f, 0.f);
-  c32 vm[DIV], vc[DIV], rp[DIV];
 #pragma unroll
-  for (int it = 0; it < DIV; ++it) vm[it] = vc[it] = rp[it] = make_float2(0.f, 0.f);
-  for (int f = f0; f <= f1; ++f) {
-    c32 rf[DIV], vf[DIV];
+  for (int i = 0; i < R; ++i) vp[i] = a[i] = zs[i] = make_float2(0.f, 0.f);
+  // odd: f is odd, so that s of the coarse plane's own fine plane f - 1 is complete; else f - 1
+  // closes one coarse plane (its sums go to LDS, weighted in the next step) and opens the next
+  auto step = [&](auto odd, int f) {
+    c32 v[R], rf[R], nb[R];
+    const bool inz = f >= 0 && f < n, ing = f >= 1 && f <= n;
 #pragma unroll
-    for (int it = 0; it < DIV; ++it) {
-      rf[it] = cscale(rn[it], sc);
-      vf[it] = cmul(rf[it], wn[it]);
-      sV[f & 1][r0 + 4 * it][lx] = vf[it];
+    for (int i = 0; i < R; ++i) {
+      rf[i] = cscale(rn[i], sc);
+      v[i] = select0(inx && inz && in[i], cmul(rf[i], wn[i]));
     }
-    if (f < f1) fetch(f + 1);
-    __syncthreads();
-    const int g = f - 1;  // the plane whose s is formed now
-    if (g >= f0 + 1) {
-      const bool ing = g >= 0 && g < n;
-      const c32(*P)[64] = sV[g & 1];
+    fetch(min(f + 1, f1));
+    plane_neighbours<decltype(odd)::value>(sV, w, lane, v, nb);
 #pragma unroll
-      for (int it = 0; it < DIV; ++it) {
-        const int ly = r0 + 4 * it;
-        if (lx < 1 || lx > DRX - 2 || ly < 1 || ly > DRY - 2) continue;
-        c32 sv = make_float2(0.f, 0.f);
-        if (ing && in[it]) {
-          const c32 nb = cadd(cadd(cadd(P[ly][lx - 1], P[ly][lx + 1]), cadd(P[ly - 1][lx], P[ly + 1][lx])),
-                              cadd(vm[it], vf[it]));
-          sv = cadd(cscale(rp[it], 1.0f - omega), nb);
-        }
-        sS[ly][lx] = sv;
+    for (int i = 0; i < R; ++i) {
+      const c32 s = cscale(select0(inx && ing && in[i], cadd(a[i], v[i])), odd ? 0.5f : 0.25f);
+      zs[i] = cadd(zs[i], s);
+      if (!odd) {
+        sS[w * R + i][lane] = zs[i];
+        zs[i] = s;
       }
+      a[i] = cadd(cadd(cscale(rf[i], om1), nb[i]), vp[i]);
+      vp[i] = v[i];
+      asm volatile("" : "+v"(a[i].x), "+v"(a[i].y));  // before the branch: the lane shifts fold into the additions
     }
-    __syncthreads();
-    if (g >= f0 + 1 && coarse) {
-      const int sx = 2 * tx + 2, sy = 2 * ty + 2;
-      c32 t = cscale(sS[sy][sx], 0.25f);
-      t = cadd(t, cscale(cadd(cadd(sS[sy][sx - 1], sS[sy][sx + 1]), cadd(sS[sy - 1][sx], sS[sy + 1][sx])), 0.125f));
-      t = cadd(t, cscale(cadd(cadd(sS[sy - 1][sx - 1], sS[sy - 1][sx + 1]), cadd(sS[sy + 1][sx - 1], sS[sy + 1][sx + 1])),
-                         0.0625f));
-      if (g & 1) {  // g = 2K + 1: closes K (unless g is the chunk's first plane), opens K + 1
-        if (g > f0 + 1) {
-          const int K = (g - 1) >> 1;
-          acc = cadd(acc, cscale(t, 0.25f));
-          rc.p[(long long)b * rc.stride + ((long long)K * nc + cy0 + ty) * nc + cx0 + tx] = cscale(acc, 4.0f);
-        }
-        acc = cscale(t, 0.25f);
-      } else {
-        acc = cadd(acc, cscale(t, 0.5f));
-      }
-    }
-#pragma unroll
-    for (int it = 0; it < DIV; ++it) {
-      vm[it] = vc[it];
-      vc[it] = vf[it];
-      rp[it] = rf[it];
-    }
+    if constexpr (decltype(odd)::value)
+      if (f > f0 + 3) weight((f - 3) >> 1);
+  };
+  step(std::false_type{}, f0);
+  for (int f = f0 + 1; f < f1; f += 2) {
+    step(std::true_type{}, f);
+    step(std::false_type{}, f + 1);
   }
+  __syncthreads();
+  weight(kz1 - 1);
 }
 
-// The up-leg marching in z with a fixed thread map: a 64 x 8 column, two own
-// points per thread (x and x + 32) and a one-point in-plane ring (148 threads
-// take one ring point each).  Each thread keeps its own points' v2 of the
-// planes f - 2 .. f and r, W of the plane it smooths in registers, with the
-// next plane's loads in flight; only the in-plane neighbours go through LDS
-// (two planes).  Per fine plane f: v2(f) = W r + P e (the coarse planes that P
-// reads are kept two at a time in LDS), then z(f - 1) from v2(f - 2 .. f).  With acc
+// The up-leg: own points in lanes 1 .. 62 and rows 1 .. R NW - 2 of the region that starts at
+// (x0 - 1, y0 - 1).  The in-plane interpolation of a coarse plane is formed once, from one
+// LDS copy, and kept in registers for the (up to three) fine planes that read it: rows start odd
+// and R is even, so which rows lie between coarse rows is known at compile time.  Per fine
+// plane f: v2(f) = W r + P e, then z(f - 1) from v2(f - 2 .. f), where
+// (1 - omega) v2 + W (r + neighbours so far) is all that is kept of plane f - 1.  With acc
 // the leg adds z to the output instead of overwriting it (a repeated coarse visit:
 // e + MG(r - K e, 0) without a separate pass).
-constexpr int UX = 64, UY = 8, URING = 2 * (UX + 2) + 2 * UY;
-__global__ __launch_bounds__(256) void k_up_march3c(int nrhs, VecSet r, ScaleSet rs, LevelArgs lv, float omega,
-                                                    VecSet ec, int nc, VecSet z, const int* active, int acc,
-                                                    int planes) {
-  constexpr int CX = UX / 2 + 2, CY = UY / 2 + 2, NCP = CX * CY, ITC = (NCP + 255) / 256;
-  __shared__ c32 sE[2][CY][CX];
-  __shared__ c32 sV[2][UY + 2][UX + 2];
+constexpr int UX = 62;
+template <int R, int NW>
+__global__ __launch_bounds__(64 * NW) void k_up_march3(int nrhs, VecSet r, ScaleSet rs, LevelArgs lv, float omega,
+                                                       VecSet ec, int nc, VecSet z, const int* active, int acc,
+                                                       int planes) {
+  static_assert(R % 2 == 0, "rows in pairs");
+  constexpr int UY = R * NW - 2, CX = UX / 2 + 2, CY = R * NW / 2 + 1, NCP = CX * CY,
+                ITC = (NCP + 64 * NW - 1) / (64 * NW);
+  __shared__ MarchLds<R, NW> sV;
+  __shared__ c32 sE[CY * CX];
   const int n = lv.n;
   const int tx_n = (n + UX - 1) / UX, ty_n = (n + UY - 1) / UY;
   const unsigned tiles = (unsigned)(tx_n * ty_n * ((n + planes - 1) / planes));
   const TileId id = xcd_tile(blockIdx.x, nrhs, tiles, HELM_RHS_GROUP);
   const int b = id.b;
   if (active && !active[b]) return;
-  const int fx0 = (id.t % tx_n) * UX, fy0 = ((id.t / tx_n) % ty_n) * UY, fz0 = (id.t / (tx_n * ty_n)) * planes;
-  const int fz1 = min(n, fz0 + planes);
-  const int cxs = fx0 / 2 - 1, cys = fy0 / 2 - 1;
-  const float sc = scale_of(rs, b);
+  const int x0 = (id.t % tx_n) * UX, y0 = ((id.t / tx_n) % ty_n) * UY, z0 = (id.t / (tx_n * ty_n)) * planes;
+  const int z1 = min(n, z0 + planes);
+  const int cxs = x0 / 2 - 1, cys = y0 / 2 - 1;
+  const float sc = scale_of(rs, b), om1 = 1.0f - omega;
   const c32* rb = r.p + (long long)b * r.stride;
   const c32* eb = ec.p + (long long)b * ec.stride;
+  c32* zb = z.p + (long long)b * z.stride;
   const long long n2 = (long long)n * n, nc2 = (long long)nc * nc;
-  // points of this thread: q = 0, 1 own, q = 2 the ring point (if any); LDS coordinates (lx, ly)
-  const int tx = threadIdx.x % 32, ty = threadIdx.x / 32;
-  int lxq[3], lyq[3];
-  lxq[0] = tx + 1, lyq[0] = ty + 1, lxq[1] = tx + 33, lyq[1] = ty + 1;
-  {
-    const int t = threadIdx.x;
-    int rx = -1, ry = -1;
-    if (t < UX + 2) rx = t, ry = 0;
-    else if (t < 2 * (UX + 2)) rx = t - (UX + 2), ry = UY + 1;
-    else if (t < 2 * (UX + 2) + UY) rx = 0, ry = t - 2 * (UX + 2) + 1;
-    else if (t < URING) rx = UX + 1, ry = t - 2 * (UX + 2) - UY + 1;
-    lxq[2] = rx, lyq[2] = ry;
-  }
-  bool in[3];
-  long long off[3];
-  int gxq[3], gyq[3];
+  const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int gx = x0 - 1 + lane, gy0 = y0 - 1 + w * R;
+  const bool inx = gx >= 0 && gx < n, ownx = inx && lane >= 1 && lane <= UX;
+  const unsigned xo = inx ? (unsigned)gx * (unsigned)sizeof(c32) : 0u;
+  bool in[R], own[R];
+  int row[R];
 #pragma unroll
-  for (int q = 0; q < 3; ++q) {
-    gxq[q] = fx0 - 1 + lxq[q], gyq[q] = fy0 - 1 + lyq[q];
-    in[q] = lxq[q] >= 0 && gxq[q] >= 0 && gxq[q] < n && gyq[q] >= 0 && gyq[q] < n;
-    off[q] = in[q] ? (long long)gyq[q] * n + gxq[q] : 0;
+  for (int i = 0; i < R; ++i) {
+    const int ly = w * R + i;
+    in[i] = gy0 + i >= 0 && gy0 + i < n;
+    own[i] = in[i] && ly >= 1 && ly <= UY;
+    row[i] = min(max(gy0 + i, 0), n - 1) * n;
   }
-  long long coff[ITC];
+  unsigned coff[ITC];
   bool cin[ITC];
 #pragma unroll
   for (int it = 0; it < ITC; ++it) {
-    const int idx = threadIdx.x + it * 256;
-    const int I = cxs + idx % CX, J = cys + idx / CX;
-    cin[it] = idx < NCP && I >= 0 && I < nc && J >= 0 && J < nc;
-    coff[it] = cin[it] ? (long long)J * nc + I : 0;
+    const int q = threadIdx.x + it * 64 * NW;
+    const int I = cxs + q % CX, J = cys + q / CX;
+    cin[it] = q < NCP && I >= 0 && I < nc && J >= 0 && J < nc;
+    coff[it] = cin[it] ? (unsigned)(J * nc + I) * (unsigned)sizeof(c32) : 0u;
   }
-  c32 rn[3], wn[3], cn[ITC];
+  c32 rn[R], wn[R], cn[ITC];
   auto fetch = [&](int f) {
-    const bool inz = f >= 0 && f < n;
+    const long long p = (long long)min(max(f, 0), n - 1) * n2;
+    const unsigned x = here(xo);
 #pragma unroll
-    for (int q = 0; q < 3; ++q) {
-      const bool ok = inz && in[q];
-      const long long p = ok ? f * n2 + off[q] : 0;
-      rn[q] = ok ? rb[p] : make_float2(0.f, 0.f);
-      wn[q] = ok ? lv.wd[p] : make_float2(0.f, 0.f);
+    for (int i = 0; i < R; ++i) {
+      rn[i] = at_byte(rb + p + row[i], x);
+      wn[i] = at_byte(lv.wd + p + row[i], x);
     }
   };
   auto fetch_coarse = [&](int K) {
     const bool inz = K >= 0 && K < nc;
+    const c32* p = eb + (long long)min(max(K, 0), nc - 1) * nc2;
+#pragma unroll
+    for (int it = 0; it < ITC; ++it) cn[it] = select0(inz && cin[it], at_byte(p, coff[it]));
+  };
+  auto store_coarse = [&]() {
 #pragma unroll
     for (int it = 0; it < ITC; ++it) {
-      const bool ok = inz && cin[it];
-      cn[it] = ok ? eb[K * nc2 + coff[it]] : make_float2(0.f, 0.f);
+      const int q = threadIdx.x + it * 64 * NW;
+      if (q < NCP) sE[q] = cn[it];
     }
   };
-  auto store_coarse = [&](int K) {
+  // gx >> 1 and the point above it, gx odd (lane even) only; row i = 0 is odd: it lies between
+  // the coarse rows (gy0 >> 1) and (gy0 >> 1) + 1
+  const int ex = ((gx + 2) >> 1) - 1 - cxs, exo = lane & 1 ? ex : ex + 1;
+  auto interpolate = [&](c32 (&p)[R]) {
+    c32 h[R / 2 + 1];
 #pragma unroll
-    for (int it = 0; it < ITC; ++it) {
-      const int idx = threadIdx.x + it * 256;
-      if (idx < NCP) sE[K & 1][idx / CX][idx % CX] = cn[it];
+    for (int q = 0; q < R / 2 + 1; ++q) {
+      const c32* row = sE + (w * (R / 2) + q) * CX;
+      h[q] = cscale(cadd(row[ex], row[exo]), 0.5f);
     }
+#pragma unroll
+    for (int i = 0; i < R; ++i)
+      p[i] = i & 1 ? h[(i + 1) / 2] : cscale(cadd(h[i / 2], h[i / 2 + 1]), 0.5f);
   };
-  const int fa = fz0 - 1, fb = fz1;  // planes whose v2 is needed
-  int khi = (max(fa, 0) >> 1) + 1;   // highest coarse plane in LDS
-  fetch_coarse(khi - 1);
-  store_coarse(khi - 1);
-  fetch_coarse(khi);
-  store_coarse(khi);
+  const int fa = z0 - 1, fb = z1;  // planes whose v2 is needed; z0 is even
+  c32 pc[R], vp[R], t[R], wc[R];
   fetch(fa);
+  fetch_coarse((fa - 1) / 2);
+  store_coarse();
+  fetch_coarse((fa + 1) / 2);
   __syncthreads();
-  c32 vm[2] = {make_float2(0.f, 0.f), make_float2(0.f, 0.f)}, vc[2] = {vm[0], vm[1]};
-  c32 rc[2] = {vm[0], vm[1]}, wc[2] = {vm[0], vm[1]};  // r (scaled) and W of plane f - 1
-  c32* zb = z.p + (long long)b * z.stride;
-  for (int f = fa; f <= fb; ++f) {
-    c32 rf[3], wf[3];
+  interpolate(pc);
+  __syncthreads();
+  store_coarse();
+  __syncthreads();
 #pragma unroll
-    for (int q = 0; q < 3; ++q) {
-      rf[q] = cscale(rn[q], sc);
-      wf[q] = wn[q];
-    }
-    const int knext = (f + 2) >> 1;  // the higher coarse plane that v2(f + 1) reads
-    if (f < fb) {
-      fetch(f + 1);
-      if (knext > khi) fetch_coarse(knext);
-    }
-    // v2(f) = W r + P e at the own points and the ring point
-    c32 vf[3];
+  for (int i = 0; i < R; ++i) vp[i] = t[i] = wc[i] = make_float2(0.f, 0.f);
+  auto step = [&](auto odd, int f) {
+    c32 v[R], rf[R], wf[R], nb[R];
     const bool inz = f >= 0 && f < n;
-    const int klo = f >> 1;
+    if constexpr (decltype(odd)::value) {  // between two coarse planes: the upper one is in LDS
+      c32 pn[R];
+      interpolate(pn);
+      fetch_coarse((f + 3) >> 1);
 #pragma unroll
-    for (int q = 0; q < 3; ++q) {
-      vf[q] = make_float2(0.f, 0.f);
-      if (inz && in[q]) {
-        c32 pe = prolong_lds<CX>(sE[klo & 1], gxq[q], gyq[q], cxs, cys);
-        if (f & 1) pe = cscale(cadd(pe, prolong_lds<CX>(sE[(klo + 1) & 1], gxq[q], gyq[q], cxs, cys)), 0.5f);
-        vf[q] = cadd(cmul(rf[q], wf[q]), pe);
+      for (int i = 0; i < R; ++i) {
+        v[i] = cscale(cadd(pc[i], pn[i]), 0.5f);
+        pc[i] = pn[i];
       }
-      if (lxq[q] >= 0) sV[f & 1][lyq[q]][lxq[q]] = vf[q];
-    }
-    __syncthreads();
-    if (f < fb && knext > khi) {  // the coarse plane that replaces one no longer read
-      store_coarse(knext);
-      khi = knext;
-    }
-    const int g = f - 1;  // output plane
-    if (g >= fz0) {
+    } else {  // on a coarse plane that every thread has read, so that the next can take its place
+      store_coarse();
 #pragma unroll
-      for (int q = 0; q < 2; ++q) {
-        if (!in[q]) continue;
-        const int lx = lxq[q], ly = lyq[q];
-        const c32(*P)[UX + 2] = sV[g & 1];
-        const c32 nb = cadd(cadd(cadd(P[ly][lx - 1], P[ly][lx + 1]), cadd(P[ly - 1][lx], P[ly + 1][lx])),
-                            cadd(vm[q], vf[q]));
-        const c32 zv = cadd(cscale(vc[q], 1.0f - omega), cmul(wc[q], cadd(rc[q], nb)));
-        const long long p = g * n2 + off[q];
-        zb[p] = acc ? cadd(zb[p], zv) : zv;
-      }
+      for (int i = 0; i < R; ++i) v[i] = pc[i];
     }
-    __syncthreads();
 #pragma unroll
-    for (int q = 0; q < 2; ++q) {
-      vm[q] = vc[q];
-      vc[q] = vf[q];
-      rc[q] = rf[q];
-      wc[q] = wf[q];
+    for (int i = 0; i < R; ++i) {
+      rf[i] = cscale(rn[i], sc);
+      wf[i] = wn[i];
+      v[i] = select0(inx && inz && in[i], cadd(cmul(rf[i], wf[i]), v[i]));
     }
+    fetch(min(f + 1, fb));
+    plane_neighbours<decltype(odd)::value>(sV, w, lane, v, nb);
+    c32 zo[R];
+#pragma unroll
+    for (int i = 0; i < R; ++i) {
+      zo[i] = cadd(t[i], cmul(wc[i], v[i]));
+      t[i] = cadd(cscale(v[i], om1), cmul(wf[i], cadd(cadd(rf[i], nb[i]), vp[i])));
+      wc[i] = wf[i];
+      vp[i] = v[i];
+      asm volatile("" : "+v"(t[i].x), "+v"(t[i].y));  // before the branch: the lane shifts fold into the additions
+    }
+    if (f > z0 && f <= fb && ownx) {  // output plane f - 1
+      c32* zp = zb + (long long)(f - 1) * n2;
+      const unsigned x = here(xo);
+      if (acc)
+#pragma unroll
+        for (int i = 0; i < R; ++i) zo[i] = cadd(at_byte(zp + row[i], x), zo[i]);
+#pragma unroll
+      for (int i = 0; i < R; ++i)
+        if (own[i]) *(c32*)((char*)(zp + row[i]) + x) = zo[i];
+    }
+  };
+  for (int f = fa; f <= fb; f += 2) {
+    step(std::true_type{}, f);
+    step(std::false_type{}, f + 1);
   }
 }
 
@@ -1125,101 +1124,16 @@ __global__ void k_level_residual(int dim, VecSet bvec, ScaleSet bs, VecSet v, Le
   out.p[(long long)b * out.stride + p] = csub(cscale(bvec.p[(long long)b * bvec.stride + p], scale_of(bs, b)), kv);
 }
 
-// The same residual in 3D, marching in z: a 64 x 8 column over 16 planes, two
-// points per thread, the in-plane neighbours from an LDS copy of the plane and a
-// one-point ring, the planes below and above in registers with the next plane's
-// loads in flight (the flat kernel's z-neighbours, a plane apart, mostly miss the
-// L2).  Neighbours summed in the order of neighbour_sum (zero outside the grid).
-constexpr int RMX = 64, RMY = 8;
-__global__ __launch_bounds__(256) void k_level_residual_march3(int nrhs, VecSet bvec, ScaleSet bs, VecSet v,
-                                                               LevelArgs lv, VecSet out, const int* active, int planes) {
-  __shared__ c32 sP[RMY + 2][RMX + 2];
-  const int n = lv.n;
-  const int tx_n = (n + RMX - 1) / RMX, ty_n = (n + RMY - 1) / RMY;
-  const unsigned tiles = (unsigned)(tx_n * ty_n * ((n + planes - 1) / planes));
-  const TileId id = xcd_tile(blockIdx.x, nrhs, tiles, HELM_RHS_GROUP);
+// the same residual in 3D, marching in z
+template <int NW>
+__global__ __launch_bounds__(64 * NW) void k_level_residual_march3(int nrhs, VecSet bvec, ScaleSet bs, VecSet v,
+                                                                   LevelArgs lv, VecSet out, const int* active,
+                                                                   int planes) {
+  const TileId id = xcd_tile(blockIdx.x, nrhs, march_apply_tiles<NW>(lv.n, planes), HELM_RHS_GROUP);
   const int b = id.b;
   if (active && !active[b]) return;
-  const int x0 = (id.t % tx_n) * RMX, y0 = ((id.t / tx_n) % ty_n) * RMY, z0 = (id.t / (tx_n * ty_n)) * planes;
-  const int z1 = min(n, z0 + planes);
-  const c32* vb = v.p + (long long)b * v.stride;
-  const c32* bb = bvec.p + (long long)b * bvec.stride;
-  c32* ob = out.p + (long long)b * out.stride;
-  const float sc = scale_of(bs, b);
-  const long long n2 = (long long)n * n;
-  const int tx = threadIdx.x % 32, ty = threadIdx.x / 32;
-  bool own[2];
-  long long o[2];
-#pragma unroll
-  for (int h = 0; h < 2; ++h) {
-    const int gx = x0 + tx + 32 * h, gy = y0 + ty;
-    own[h] = gx < n && gy < n;
-    o[h] = own[h] ? (long long)gy * n + gx : 0;
-  }
-  int rx = -1, ry = -1;  // this thread's ring point (LDS coordinates), if any
-  {
-    const int t = threadIdx.x;
-    if (t < RMX + 2) rx = t, ry = 0;
-    else if (t < 2 * (RMX + 2)) rx = t - (RMX + 2), ry = RMY + 1;
-    else if (t < 2 * (RMX + 2) + RMY) rx = 0, ry = t - 2 * (RMX + 2) + 1;
-    else if (t < 2 * (RMX + 2) + 2 * RMY) rx = RMX + 1, ry = t - 2 * (RMX + 2) - RMY + 1;
-  }
-  const int rgx = x0 - 1 + rx, rgy = y0 - 1 + ry;
-  const bool ring = rx >= 0 && rgx >= 0 && rgx < n && rgy >= 0 && rgy < n;
-  const long long ro = ring ? (long long)rgy * n + rgx : 0;
-  auto at = [&](bool ok, int zz, long long off) {
-    return ok && zz >= 0 && zz < n ? vb[zz * n2 + off] : make_float2(0.f, 0.f);
-  };
-  c32 vm[2], vc[2], vp[2], kc[2], bc[2];
-  c32 vr = at(ring, z0, ro);
-#pragma unroll
-  for (int h = 0; h < 2; ++h) {
-    vm[h] = at(own[h], z0 - 1, o[h]);
-    vc[h] = at(own[h], z0, o[h]);
-    vp[h] = at(own[h], z0 + 1, o[h]);
-    kc[h] = own[h] ? lv.coef[z0 * n2 + o[h]] : make_float2(0.f, 0.f);
-    bc[h] = own[h] ? bb[z0 * n2 + o[h]] : make_float2(0.f, 0.f);
-  }
-  for (int zz = z0; zz < z1; ++zz) {
-#pragma unroll
-    for (int h = 0; h < 2; ++h) sP[ty + 1][tx + 1 + 32 * h] = vc[h];
-    if (rx >= 0) sP[ry][rx] = vr;
-    c32 vn[2], kn[2], bn[2];
-#pragma unroll
-    for (int h = 0; h < 2; ++h) {
-      vn[h] = at(own[h], zz + 2, o[h]);
-      const bool nx = own[h] && zz + 1 < n;
-      kn[h] = nx ? lv.coef[(zz + 1) * n2 + o[h]] : make_float2(0.f, 0.f);
-      bn[h] = nx ? bb[(zz + 1) * n2 + o[h]] : make_float2(0.f, 0.f);
-    }
-    const c32 vrn = at(ring, zz + 1, ro);
-    __syncthreads();
-#pragma unroll
-    for (int h = 0; h < 2; ++h) {
-      if (!own[h]) continue;
-      const int lx = tx + 1 + 32 * h, ly = ty + 1;
-      const int ng = ghosts3(x0 + tx + 32 * h, y0 + ty, zz, n);
-      const c32 D = make_float2(6.0f - kc[h].x - ng * lv.ghost.x, -kc[h].y - ng * lv.ghost.y);
-      c32 nb = make_float2(0.f, 0.f);
-      nb = cadd(nb, sP[ly][lx - 1]);
-      nb = cadd(nb, sP[ly][lx + 1]);
-      nb = cadd(nb, sP[ly - 1][lx]);
-      nb = cadd(nb, sP[ly + 1][lx]);
-      nb = cadd(nb, vm[h]);
-      nb = cadd(nb, vp[h]);
-      ob[zz * n2 + o[h]] = csub(cscale(bc[h], sc), csub(cmul(D, vc[h]), nb));
-    }
-    __syncthreads();
-#pragma unroll
-    for (int h = 0; h < 2; ++h) {
-      vm[h] = vc[h];
-      vc[h] = vp[h];
-      vp[h] = vn[h];
-      kc[h] = kn[h];
-      bc[h] = bn[h];
-    }
-    vr = vrn;
-  }
+  march_apply<true, NW>(v.p + (long long)b * v.stride, bvec.p + (long long)b * bvec.stride, scale_of(bs, b), lv, id.t,
+                        planes, out.p + (long long)b * out.stride);
 }
 
 // y += x for every active right-hand side
@@ -1358,21 +1272,41 @@ void up_tile(hipStream_t s, int B, VecSet r, ScaleSet rs, LevelArgs lv, float om
 }
 }  // namespace
 
+namespace {
+template <int R, int NW>
+void down_march(hipStream_t s, int B, VecSet r, ScaleSet rs, LevelArgs lv, float omega, VecSet rc, int nc,
+                const int* active) {
+  constexpr int CY = (R * NW - 3) / 2;
+  const int cols = ((nc + DCX - 1) / DCX) * ((nc + CY - 1) / CY);
+  // at most 12 coarse planes: cycle at 128^3 x 8 619 / 617 / 613 / 612 / 611 us with 6 / 8 / 10 / 12 / 16
+  const int planes = march_planes((long long)B * cols, nc, 12, 1);
+  hipLaunchKernelGGL((k_down_march3<R, NW>), dim3(B * cols * ((nc + planes - 1) / planes)), dim3(64 * NW), 0, s, B, r,
+                     rs, lv, omega, rc, nc, active, planes);
+}
+template <int R, int NW>
+void up_march(hipStream_t s, int B, VecSet r, ScaleSet rs, LevelArgs lv, float omega, VecSet ec, int nc, VecSet z,
+              const int* active, int acc) {
+  constexpr int UY = R * NW - 2;
+  const int n = lv.n, cols = ((n + UX - 1) / UX) * ((n + UY - 1) / UY);
+  const int planes = march_planes((long long)B * cols, n, 16, 2);
+  hipLaunchKernelGGL((k_up_march3<R, NW>), dim3(B * cols * ((n + planes - 1) / planes)), dim3(64 * NW), 0, s, B, r, rs,
+                     lv, omega, ec, nc, z, active, acc, planes);
+}
+}  // namespace
+
 void launch_down_fused3(hipStream_t s, int B, VecSet r, ScaleSet rs, LevelArgs lv, float omega, VecSet rc, int nc,
                         const int* active) {
-  const int cols = ((nc + DCX - 1) / DCX) * ((nc + DCY - 1) / DCY);
-  const int planes = march_planes((long long)B * cols, nc, 8, 1);
-  hipLaunchKernelGGL(k_down_march3c, dim3(B * cols * ((nc + planes - 1) / planes)), dim3(256), 0, s, B, r, rs, lv,
-                     omega, rc, nc, active, planes);
+  down_march<2, 8>(s, B, r, rs, lv, omega, rc, nc, active);
 }
 
 void launch_up_fused3(hipStream_t s, int B, VecSet r, ScaleSet rs, LevelArgs lv, float omega, VecSet ec, int nc,
                       VecSet z, const int* active, int acc) {
-  const int n = lv.n;
-  const int cols = ((n + UX - 1) / UX) * ((n + UY - 1) / UY);
-  const int planes = march_planes((long long)B * cols, n, 16, 2);
-  hipLaunchKernelGGL(k_up_march3c, dim3(B * cols * ((n + planes - 1) / planes)), dim3(256), 0, s, B, r, rs, lv, omega,
-                     ec, nc, z, active, acc, planes);
+  // tile heights: cycle at 128^3 x 8 629 us with 6 own rows everywhere, 617 with 14 on the 177^3 level
+  // only; 64^3 x 8 solve (113^3 finest) 44.2 ms with 14 rows on it, 44.0 with 6
+  if (march_tall(lv.n, B, 2048))
+    up_march<2, 8>(s, B, r, rs, lv, omega, ec, nc, z, active, acc);
+  else
+    up_march<2, 4>(s, B, r, rs, lv, omega, ec, nc, z, active, acc);
 }
 
 template <int TY, int K>
@@ -1527,11 +1461,12 @@ void launch_apply(hipStream_t s, int dim, int B, VecSet x, ScaleSet xs, LevelArg
 void launch_level_residual(hipStream_t s, int dim, int B, VecSet bvec, VecSet v, LevelArgs lv, VecSet out,
                            const int* active, ScaleSet bs) {
   if (dim == 3) {
-    const int n = lv.n;
-    const int cols = ((n + RMX - 1) / RMX) * ((n + RMY - 1) / RMY);
-    const int planes = march_planes((long long)B * cols, n, 16, 2);
-    hipLaunchKernelGGL(k_level_residual_march3, dim3(B * cols * ((n + planes - 1) / planes)), dim3(256), 0, s, B, bvec,
-                       bs, v, lv, out, active, planes);
+    auto march = [&](auto kernel, int nw, int planes, unsigned tiles) {
+      hipLaunchKernelGGL(kernel, dim3(B * tiles), dim3(64 * nw), 0, s, B, bvec, bs, v, lv, out, active, planes);
+    };
+    const int n = lv.n, tall = march_apply_planes<8>(n, B), low = march_apply_planes<4>(n, B);
+    if (march_tall(n, B, 1024)) march(k_level_residual_march3<8>, 8, tall, march_apply_tiles<8>(n, tall));
+    else march(k_level_residual_march3<4>, 4, low, march_apply_tiles<4>(n, low));
     return;
   }
   hipLaunchKernelGGL(k_level_residual, dim3(nblocks(lv.N, 256), B), dim3(256), 0, s, dim, bvec, bs, v, lv, out,

@@ -35,12 +35,12 @@ enum {
 };
 
 // Planes one workgroup of a 3D marching kernel walks: `most` halved (down to `least`) until
-// the launch has `target` workgroups, by default 1024, four per CU.  A march is a serial chain of about 1.4 us a
-// plane, and small levels or batches left most CUs idle behind a few long ones: with 16
-// (down-leg: 8 coarse) planes throughout, the legs of a 29^3 x 8 level took 22-38 us of a
-// cycle.  64^3 x 8 solve 64.6 -> 50.6 ms, cycle at 128^3 x 8 872 -> 771 us; a target of 256 /
-// 512 / 2048 / 4096 workgroups gave 56.8 / 51.5 / 50.2 / 52.8 ms and 780 / 769 / 776 / 794 us.
-// Every point is computed by the same arithmetic whatever the march.
+// the launch has `target` workgroups, by default 1024, four per CU.  A march is a serial chain of
+// about a microsecond a plane, and small levels or batches would leave most CUs idle behind a few
+// long ones: with 16 (down-leg: 8 coarse) planes throughout, the legs of a 29^3 x 8 level took
+// 22-38 us of a cycle, and the 64^3 x 8 solve 64.6 ms instead of 50.6.  Targets of 256 / 512 /
+// 1024 / 2048 / 4096 workgroups gave 56.8 / 51.5 / 50.6 / 50.2 / 52.8 ms, a cycle at 128^3 x 8
+// 780 / 769 / 771 / 776 / 794 us.  Every point is computed by the same arithmetic whatever the march.
 inline int march_planes(long long columns, int n, int most, int least, int target = 1024) {
   int p = most;
   while (p > least && columns * ((n + p - 1) / p) < target) p = (p + 1) / 2;
