@@ -201,9 +201,15 @@ void set_current(helm_net* n, int nimg, int D0, int H0, int W0) {
 // rows of the backward-data weights: the input channels rounded up to whole 16-channel tiles
 int wb_rows(const NetLayer& L) { return round_up(L.cin_pad, 16); }
 
-void pack(helm_net* n, int i) {
-  NetLayer& L = n->L[i];
-  launch_pack(n->s, n->ntaps, L.cout_pad, L.cin_pad, L.kpad, L.cob, L.kbpad, wb_rows(L), L.w, L.wt, L.wb);
+void pack(helm_net* n, int first, int count) {
+  PackArgs a{};
+  a.n = count;
+  a.ntaps = n->ntaps;
+  for (int i = 0; i < count; ++i) {
+    NetLayer& L = n->L[first + i];
+    a.L[i] = PackLayer{L.cout_pad, L.cin_pad, L.kpad, L.cob, L.kbpad, wb_rows(L), L.w, L.wt, L.wb, 0};
+  }
+  launch_pack(n->s, a);
 }
 
 // plain input: in[p][0, ct)
@@ -457,7 +463,7 @@ int create(unsigned long long seed, void* hip_stream, int dim, helm_net** out) {
       ck(hipMemcpy(L.b, zero.data(), L.cout * 4, hipMemcpyHostToDevice), "upload");
       ck(hipMemcpy(L.mb, zero.data(), L.cout * 4, hipMemcpyHostToDevice), "upload");
       ck(hipMemcpy(L.vb, zero.data(), L.cout * 4, hipMemcpyHostToDevice), "upload");
-      pack(n, i);
+      pack(n, i, 1);
     }
     ck(hipStreamSynchronize(n->s), "sync");
   } catch (const NetErr& e) {
@@ -594,7 +600,7 @@ int helm_net_set_layer(helm_net* n, int i, const float* w_host, const float* b_h
         w[(size_t)co * L.kpad + tap * L.cin_pad + ci] = w_host[((size_t)tap * L.cin + ci) * L.cout + co];
   ck(hipMemcpy(L.w, w.data(), w.size() * 4, hipMemcpyHostToDevice), "upload");
   ck(hipMemcpy(L.b, b_host, L.cout * 4, hipMemcpyHostToDevice), "upload");
-  pack(n, i);
+  pack(n, i, 1);
   ck(hipStreamSynchronize(n->s), "sync");
   NET_CATCH
   return HELM_OK;
@@ -686,12 +692,14 @@ int helm_net_adam_step(helm_net* n, double lr) {
   const float b1 = 0.9f, b2 = 0.999f, eps = 1e-8f;
   const float c1 = (float)(1.0 / (1.0 - std::pow(0.9, n->step)));
   const float c2 = (float)(1.0 / (1.0 - std::pow(0.999, n->step)));
+  AdamArgs a{2 * HELM_NET_LAYERS, (float)lr, b1, b2, eps, c1, c2, {}};
   for (int i = 0; i < HELM_NET_LAYERS; ++i) {
     NetLayer& L = n->L[i];
-    launch_adam(n->s, L.cout_pad * L.kpad, L.w, L.dw, L.mw, L.vw, L.mask, (float)lr, b1, b2, eps, c1, c2);
-    launch_adam(n->s, L.cout, L.b, L.db, L.mb, L.vb, nullptr, (float)lr, b1, b2, eps, c1, c2);
-    pack(n, i);
+    a.T[2 * i] = AdamTensor{L.w, L.dw, L.mw, L.vw, L.mask, L.cout_pad * L.kpad, 0};
+    a.T[2 * i + 1] = AdamTensor{L.b, L.db, L.mb, L.vb, nullptr, L.cout, 0};
   }
+  launch_adam(n->s, a);
+  pack(n, 0, HELM_NET_LAYERS);
   ck(hipGetLastError(), "launch");
   ck(hipStreamSynchronize(n->s), "sync");
   NET_CATCH

@@ -90,12 +90,33 @@ void launch_res_loss(hipStream_t s, int dim, int nimg, int D, int H, int W, cons
 // per image: interior sums of |r - gamma A' y|^2 and |r|^2 into sums[2 img], sums[2 img + 1] (FP64)
 void launch_res_ratio(hipStream_t s, int dim, int nimg, int D, int H, int W, const float* x, const float* y,
                       float gamma, c32 cb, double* sums);
-void launch_adam(hipStream_t s, int n, float* w, const float* dw, float* m, float* v, const unsigned char* mask,
-                 float lr, float b1, float b2, float eps, float c1, float c2);
-// forward weights (bf16) and flipped backward-data weights over ntaps = 9 or 27 taps; wb has
-// wb_rows >= cin rows (the rows past cin are zero)
-void launch_pack(hipStream_t s, int ntaps, int cout_pad, int cin, int kpad, int cob, int kbpad, int wb_rows,
-                 const float* w, bf16* wt, bf16* wb);
+// Adam on several tensors (every layer's weights and biases) in one launch
+struct AdamTensor {
+  float* w;
+  const float* dw;
+  float *m, *v;
+  const unsigned char* mask;  // NULL: every entry is a weight
+  int count, block0;
+};
+struct AdamArgs {
+  int n;
+  float lr, b1, b2, eps, c1, c2;
+  AdamTensor T[16];
+};
+void launch_adam(hipStream_t s, AdamArgs& a);
+// forward weights (bf16) and flipped backward-data weights over ntaps = 9 or 27 taps of several
+// layers in one launch; wb has wb_rows >= cin rows (the rows past cin are zero)
+struct PackLayer {
+  int cout_pad, cin, kpad, cob, kbpad, wb_rows;
+  const float* w;
+  bf16 *wt, *wb;
+  int block0;
+};
+struct PackArgs {
+  int n, ntaps;
+  PackLayer L[8];
+};
+void launch_pack(hipStream_t s, PackArgs& a);
 void launch_net_input(hipStream_t s, int B, long long N, const c32* v, long long v_stride, const float* vscale,
                       int vs_stride, float gain, const c32* coef, c32 cb, bf16* x, int x_ct);
 void launch_net_output(hipStream_t s, int B, long long N, const float* y, float gain, c32* z, long long z_stride,
