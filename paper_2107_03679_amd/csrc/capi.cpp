@@ -466,25 +466,26 @@ void arnoldi_step(helm_ctx* c, int B, int j) {
     ProfScope ps(c, "arnoldi_matvec_dots", Bp * (16.0 + 8.0 * nv) * N + 8.0 * N);
     launch_arnoldi_dots(c->s, B, k, j, &A, 1);
   }
-  {
+  const bool own = arnoldi_update_reduces(k);
+  if (!own) {
     ProfScope ps(c, "arnoldi_reduce", red_bytes);
     launch_arnoldi_reduce(c->s, B, k, j, 0);
   }
   {
     ProfScope ps(c, "arnoldi_update", Bp * (16.0 + 8.0 * nv) * N);
-    launch_arnoldi_update(c->s, B, k, j);
+    launch_arnoldi_update(c->s, B, k, j, 0);
   }
   if (c->o.reorth) {
     {
       ProfScope ps(c, "arnoldi_dots_reorth", Bp * (8.0 + 8.0 * nv) * N);
       launch_arnoldi_dots(c->s, B, k, j, &A, 0);
     }
-    {
+    if (!own) {
       ProfScope ps(c, "arnoldi_reduce", red_bytes);
       launch_arnoldi_reduce(c->s, B, k, j, 1);
     }
     ProfScope ps(c, "arnoldi_update", Bp * (16.0 + 8.0 * nv) * N);
-    launch_arnoldi_update(c->s, B, k, j);
+    launch_arnoldi_update(c->s, B, k, j, 1);
   }
   ProfScope ps(c, "givens", Bp * k.nblk * 4.0);
   launch_givens(c->s, B, k, j);

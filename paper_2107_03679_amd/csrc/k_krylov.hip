@@ -128,9 +128,14 @@ __global__ __launch_bounds__(NT) void k_arnoldi_reduce(KrylovArgs k, int j, int 
   }
 }
 
-// w -= sum_i coef_i V_i; partial ||w||^2
-__global__ __launch_bounds__(NT) void k_arnoldi_update(KrylovArgs k, int j) {
+// w -= sum_i coef_i V_i; partial ||w||^2.  With REDUCE every workgroup forms the coefficients from
+// the partial dots itself, as k_arnoldi_reduce does and in its order, while its loads of w are
+// underway (the first one stores H); at most HELM_WAVE partials a dot, one load a lane.  Each
+// launch between the dots and the rotations cost 4-7 us of a 105 us step at 203^2 x 7.
+template <bool REDUCE>
+__global__ __launch_bounds__(NT) void k_arnoldi_update(KrylovArgs k, int j, int accumulate) {
   __shared__ float red[NWAVE];
+  __shared__ c32 sc[REDUCE ? MAXM : 1];
   const int b = blockIdx.y;
   if (!k.active[b]) return;
   const long long p0 = (long long)blockIdx.x * CH + threadIdx.x;
@@ -151,9 +156,27 @@ __global__ __launch_bounds__(NT) void k_arnoldi_update(KrylovArgs k, int j) {
   };
   c32 vc[PPT], vn[PPT];
   ldv(0, vc);
+  if constexpr (REDUCE) {
+    const int lane = threadIdx.x % HELM_WAVE, wave = threadIdx.x / HELM_WAVE;
+    for (int i = wave; i <= j; i += NWAVE) {
+      const c32 v = k.P1[((long long)b * k.nblk + min(lane, k.nblk - 1)) * (k.m + 1) + i];
+      const double sx = wave_sum_d(lane < k.nblk ? (double)v.x : 0.0);
+      const double sy = wave_sum_d(lane < k.nblk ? (double)v.y : 0.0);
+      if (lane == 0) {
+        const double vsi = k.vs[b * (k.m + 1) + i];
+        const double hx = sx * vsi, hy = sy * vsi;
+        sc[i] = make_float2((float)(hx * vsi), (float)(hy * vsi));
+        if (blockIdx.x == 0) {
+          double2* hij = &k.H[((long long)b * (k.m + 1) + i) * k.m + j];
+          *hij = accumulate ? make_double2(hij->x + hx, hij->y + hy) : make_double2(hx, hy);
+        }
+      }
+    }
+    __syncthreads();
+  }
   for (int i = 0; i <= j; ++i) {
     if (i + 1 <= j) ldv(i + 1, vn);
-    const c32 ci = k.coef[b * (k.m + 1) + i];
+    const c32 ci = REDUCE ? sc[i] : k.coef[b * (k.m + 1) + i];
     const c32 nci = make_float2(-ci.x, -ci.y);
 #pragma unroll
     for (int t = 0; t < PPT; ++t) w[t] = cfma(nci, vc[t], w[t]);
@@ -187,85 +210,111 @@ __device__ __forceinline__ double2 zmul(double2 a, double2 b) {
 __device__ __forceinline__ double2 zconj(double2 a) { return make_double2(a.x, -a.y); }
 __device__ __forceinline__ double zabs(double2 a) { return hypot(a.x, a.y); }
 
-// Back-substitution y = H(0:kk, 0:kk)^-1 g(0:kk) for right-hand side b (FP64, one thread;
-// yd: kk FP64 slots in LDS, where a per-thread array indexed at run time would spill).
-// y of the kk-column triangular system H y = g (H row stride m), written to k.y
-__device__ void back_substitute(const KrylovArgs& k, int b, int kk, double2* yd, const double2* H, const double2* g) {
-  for (int i = kk - 1; i >= 0; --i) {
-    double2 s = g[i];
-    for (int l = i + 1; l < kk; ++l) {
-      const double2 t = zmul(H[i * k.m + l], yd[l]);
+// Back-substitution y = H(0:kk, 0:kk)^-1 g(0:kk) for right-hand side b into k.y (FP64; H row
+// stride m), by one wavefront: lane i keeps row i's remaining sum, and each solved unknown is
+// taken out of the rows above it at once, the next column's entries in flight.
+__device__ void back_substitute(const KrylovArgs& k, int b, int kk, const double2* H, const double2* g) {
+  const int i = threadIdx.x, row = min(i, kk - 1);
+  double2 s = g[row], y = make_double2(0.0, 0.0), hn = H[row * k.m + kk - 1];
+  const double2 d = H[row * k.m + row];
+  const double den = d.x * d.x + d.y * d.y;
+  for (int c = kk - 1; c >= 0; --c) {
+    const double2 h = hn;
+    hn = H[row * k.m + max(c - 1, 0)];
+    const double2 q = make_double2((s.x * d.x + s.y * d.y) / den, (s.y * d.x - s.x * d.y) / den);
+    const double2 yc = make_double2(__shfl(q.x, c, HELM_WAVE), __shfl(q.y, c, HELM_WAVE));
+    const double2 t = zmul(h, yc);
+    if (i < c) {
       s.x -= t.x;
       s.y -= t.y;
     }
-    const double2 d = H[i * k.m + i];
-    const double den = d.x * d.x + d.y * d.y;
-    yd[i] = make_double2((s.x * d.x + s.y * d.y) / den, (s.y * d.x - s.x * d.y) / den);
+    if (i == c) y = q;
   }
-  for (int i = 0; i < k.m; ++i)
-    k.y[b * k.m + i] = i < kk ? make_float2((float)yd[i].x, (float)yd[i].y) : make_float2(0.f, 0.f);
+  if (i < k.m) k.y[b * k.m + i] = make_float2((float)y.x, (float)y.y);
 }
 
 // Givens update of column j (FP64), residual estimate, stop decision, least squares at cycle end.
+// The column and the earlier rotations are read by all lanes at once (one lane fetching them as
+// it went waited for memory at every rotation: 6.7 us a launch at 203^2 x 7, j < 30); the chain of
+// rotations itself is one lane's.
 __global__ __launch_bounds__(HELM_WAVE) void k_givens(KrylovArgs k, int j) {
-  __shared__ double2 yd[MAXM];
-  const int b = blockIdx.x;
+  static_assert(MAXM <= HELM_WAVE, "one lane per row");
+  __shared__ double2 hc[MAXM], ssn[MAXM];
+  __shared__ double scs[MAXM];
+  __shared__ int last;
+  const int b = blockIdx.x, lane = threadIdx.x;
   if (!k.active[b]) return;
-  double s = 0.0;
-  for (int blk = threadIdx.x; blk < k.nblk; blk += HELM_WAVE) s += k.P2[(long long)b * k.nblk + blk];
-  s = wave_sum_d(s);
-  if (threadIdx.x != 0) return;
   const int m = k.m;
   double2* H = k.H + (long long)b * (m + 1) * m;
   double* cs = k.cs + (long long)b * m;
   double2* sn = k.sn + (long long)b * m;
   double2* g = k.g + (long long)b * (m + 1);
-  const double hj1 = sqrt(s);
-  // previous rotations G_i = [[c, s], [-conj(s), c]] on rows i, i+1
-  for (int i = 0; i < j; ++i) {
-    const double2 a = H[i * m + j], c2 = H[(i + 1) * m + j];
-    const double2 t1 = zmul(sn[i], c2);
-    const double2 t2 = zmul(zconj(sn[i]), a);
-    H[i * m + j] = make_double2(cs[i] * a.x + t1.x, cs[i] * a.y + t1.y);
-    H[(i + 1) * m + j] = make_double2(cs[i] * c2.x - t2.x, cs[i] * c2.y - t2.y);
+  if (lane <= j) hc[lane] = H[lane * m + j];
+  if (lane < j) {
+    scs[lane] = cs[lane];
+    ssn[lane] = sn[lane];
   }
-  const double2 a = H[j * m + j];
-  const double aa = zabs(a);
-  double c;
-  double2 sv;
-  if (hj1 == 0.0) {
-    c = 1.0;
-    sv = make_double2(0.0, 0.0);
-  } else if (aa == 0.0) {
-    c = 0.0;
-    sv = make_double2(1.0, 0.0);
-  } else {
-    const double rho = hypot(aa, hj1);
-    c = aa / rho;
-    sv = make_double2(a.x / aa * hj1 / rho, a.y / aa * hj1 / rho);  // (a/|a|) conj(hj1) / rho, hj1 real
+  double s = 0.0;
+  for (int blk = lane; blk < k.nblk; blk += HELM_WAVE) s += k.P2[(long long)b * k.nblk + blk];
+  s = wave_sum_d(s);
+  __syncthreads();
+  if (lane == 0) {
+    last = 0;
+    const double hj1 = sqrt(s);
+    // previous rotations G_i = [[c, s], [-conj(s), c]] on rows i, i+1
+    double2 a = hc[0];
+    for (int i = 0; i < j; ++i) {
+      const double2 c2 = hc[i + 1], sni = ssn[i];
+      const double ci = scs[i];
+      const double2 t1 = zmul(sni, c2);
+      const double2 t2 = zmul(zconj(sni), a);
+      hc[i] = make_double2(ci * a.x + t1.x, ci * a.y + t1.y);
+      a = make_double2(ci * c2.x - t2.x, ci * c2.y - t2.y);
+    }
+    const double aa = zabs(a);
+    double c;
+    double2 sv;
+    if (hj1 == 0.0) {
+      c = 1.0;
+      sv = make_double2(0.0, 0.0);
+    } else if (aa == 0.0) {
+      c = 0.0;
+      sv = make_double2(1.0, 0.0);
+    } else {
+      const double rho = hypot(aa, hj1);
+      c = aa / rho;
+      sv = make_double2(a.x / aa * hj1 / rho, a.y / aa * hj1 / rho);  // (a/|a|) conj(hj1) / rho, hj1 real
+    }
+    cs[j] = c;
+    sn[j] = sv;
+    const double2 hjj = make_double2(c * a.x + sv.x * hj1, c * a.y + sv.y * hj1);
+    hc[j] = hjj;
+    H[(j + 1) * m + j] = make_double2(0.0, 0.0);
+    const double2 gj = g[j];
+    const double2 t = zmul(zconj(sv), gj);
+    const double2 gn = make_double2(-t.x, -t.y);
+    g[j + 1] = gn;
+    g[j] = make_double2(c * gj.x, c * gj.y);
+    const double est = zabs(gn);
+    const int it = ++k.iters[b];
+    k.jcount[b] = j + 1;
+    if (!isfinite(est) || !isfinite(hj1) || !isfinite(zabs(hjj))) {
+      // discard this step: the last good least-squares solution is the previous column set
+      k.status[b] = HELM_STATUS_BREAKDOWN_DEV;
+      k.active[b] = 0;
+      k.jcount[b] = 0;
+    } else {
+      k.vs[b * (m + 1) + j + 1] = hj1 > 0.0 ? (float)(1.0 / hj1) : 0.0f;
+      const bool stop = est <= k.tol[b] || hj1 == 0.0 || it >= k.max_iters;
+      if (stop) k.active[b] = 0;
+      last = stop || j == m - 1;
+    }
   }
-  cs[j] = c;
-  sn[j] = sv;
-  H[j * m + j] = make_double2(c * a.x + sv.x * hj1, c * a.y + sv.y * hj1);
-  H[(j + 1) * m + j] = make_double2(0.0, 0.0);
-  const double2 gj = g[j];
-  const double2 t = zmul(zconj(sv), gj);
-  g[j + 1] = make_double2(-t.x, -t.y);
-  g[j] = make_double2(c * gj.x, c * gj.y);
-  const double est = zabs(g[j + 1]);
-  const int it = ++k.iters[b];
-  k.jcount[b] = j + 1;
-  if (!isfinite(est) || !isfinite(hj1) || !isfinite(zabs(H[j * m + j]))) {
-    // discard this step: the last good least-squares solution is the previous column set
-    k.status[b] = HELM_STATUS_BREAKDOWN_DEV;
-    k.active[b] = 0;
-    k.jcount[b] = 0;
-    return;
-  }
-  k.vs[b * (m + 1) + j + 1] = hj1 > 0.0 ? (float)(1.0 / hj1) : 0.0f;
-  const bool stop = est <= k.tol[b] || hj1 == 0.0 || it >= k.max_iters;
-  if (stop) k.active[b] = 0;
-  if (stop || j == m - 1) back_substitute(k, b, j + 1, yd, H, g);
+  __syncthreads();
+  if (lane <= j) H[lane * m + j] = hc[lane];
+  if (!last) return;
+  __syncthreads();  // H and g as written
+  back_substitute(k, b, j + 1, H, g);
 }
 
 // x += sum_{i < jcount} y_i Z_i, accumulated into the float-float pair (x_hi, x_lo)
@@ -1153,11 +1202,13 @@ void launch_arnoldi_dots(hipStream_t s, int B, const KrylovArgs& k, int j, const
   LevelArgs lv = fine ? *fine : LevelArgs{};
   hipLaunchKernelGGL(k_arnoldi_dots, dim3(B * k.nblk), dim3(NT), 0, s, B, k, j, lv, with_matvec);
 }
+bool arnoldi_update_reduces(const KrylovArgs& k) { return k.nblk <= HELM_WAVE; }
 void launch_arnoldi_reduce(hipStream_t s, int B, const KrylovArgs& k, int j, int accumulate) {
   hipLaunchKernelGGL(k_arnoldi_reduce, dim3(B), dim3(NT), 0, s, k, j, accumulate);
 }
-void launch_arnoldi_update(hipStream_t s, int B, const KrylovArgs& k, int j) {
-  hipLaunchKernelGGL(k_arnoldi_update, dim3(k.nblk, B), dim3(NT), 0, s, k, j);
+void launch_arnoldi_update(hipStream_t s, int B, const KrylovArgs& k, int j, int accumulate) {
+  const auto kernel = arnoldi_update_reduces(k) ? k_arnoldi_update<true> : k_arnoldi_update<false>;
+  hipLaunchKernelGGL(kernel, dim3(k.nblk, B), dim3(NT), 0, s, k, j, accumulate);
 }
 void launch_givens(hipStream_t s, int B, const KrylovArgs& k, int j) {
   hipLaunchKernelGGL(k_givens, dim3(B), dim3(HELM_WAVE), 0, s, k, j);

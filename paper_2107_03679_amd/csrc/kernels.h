@@ -158,7 +158,10 @@ struct KrylovArgs {
 
 void launch_arnoldi_dots(hipStream_t s, int B, const KrylovArgs& k, int j, const LevelArgs* fine, int with_matvec);
 void launch_arnoldi_reduce(hipStream_t s, int B, const KrylovArgs& k, int j, int accumulate);
-void launch_arnoldi_update(hipStream_t s, int B, const KrylovArgs& k, int j);
+// true: launch_arnoldi_update forms the coefficients itself, launch_arnoldi_reduce is left out (up
+// to 64 blocks a right-hand side: each block reads all partial dots, one per lane)
+bool arnoldi_update_reduces(const KrylovArgs& k);
+void launch_arnoldi_update(hipStream_t s, int B, const KrylovArgs& k, int j, int accumulate);
 void launch_givens(hipStream_t s, int B, const KrylovArgs& k, int j);
 void launch_x_update(hipStream_t s, int B, const KrylovArgs& k, c32* x_hi, c32* x_lo);
 // partial squared norms per right-hand side that launch_residual_ff writes (block or column tiles)
