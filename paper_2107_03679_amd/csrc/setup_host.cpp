@@ -13,7 +13,6 @@
 
 #include <algorithm>
 #include <cmath>
-#include <thread>
 
 namespace helm_host {
 
