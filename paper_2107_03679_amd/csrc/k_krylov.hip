@@ -5,7 +5,7 @@
 // One Arnoldi step j for right-hand side q:
 //   z_j = M(v_j)                       (multigrid kernels)
 //   w   = A z_j,  d_i = <V_i, w>       (k_arnoldi_dots, fused matvec + dots)
-//   h_i = vs_i d_i                     (k_arnoldi_reduce, FP64)
+//   h_i = vs_i d_i                     (FP64; in k_arnoldi_update, large grids k_arnoldi_reduce)
 //   w  -= sum_i h_i v_i, ||w||^2       (k_arnoldi_update)
 //   Givens update of column j, residual estimate, v_{j+1} = w / h_{j+1,j}
 //                                      (k_givens, FP64, one wavefront per RHS)
