@@ -39,7 +39,8 @@ HIP_KERNEL = {
 }
 # sources the kernels are built from (any change voids a traffic record)
 SOURCES = ["paper_2107_03679_amd/csrc/k_multigrid.hip", "paper_2107_03679_amd/csrc/k_krylov.hip",
-           "paper_2107_03679_amd/csrc/dev_common.h", "paper_2107_03679_amd/csrc/kernels.h"]
+           "paper_2107_03679_amd/csrc/dev_common.h", "paper_2107_03679_amd/csrc/kernels.h",
+           "paper_2107_03679_amd/csrc/march3.h"]
 PMC_REGEX = ("k_up_mv2|k_up_fused2|k_down_fused2|k_up_col|k_down_col|k_sstep|k_residual_ff|k_x_update|k_coarse_cycle|"
              "copyBuffer|elementwise")
 
