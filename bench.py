@@ -575,7 +575,7 @@ def main():
     el_u = (time.perf_counter() - t0) / len(t_upd)
     out["with_update_n"] = {"value": B / el_u, "unit": "solves/s", "update_n_ms": 1e3 * float(np.median(t_upd)),
                             "all_converged": bool(st_u.converged),
-                            "note": "helm_update_n (medium set-up on the GPU, coarsest inverse on the host) + "
+                            "note": "helm_update_n (medium set-up on the GPU) + "
                                     "right-hand sides + batched solve, per step"}
     if args.workload == "inverse256x32":
         out["gradient"] = gradient_leg(ctx, dirs, nmap)
