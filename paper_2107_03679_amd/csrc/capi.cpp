@@ -119,8 +119,8 @@ struct helm_ctx {
 
   // launch shapes (helm_autotune): fused-leg tile per level, single-launch coarse threshold
   int tune_down[HELM_MAX_LEVELS] = {0};
-  int tune_up[HELM_MAX_LEVELS] = {0};
-  int tune_mv = 0;  // launch-shape variant (rows, right-hand sides per block) of the fused finest up-leg + matvec
+  int tune_up[HELM_MAX_LEVELS];  // < 0: by launch size
+  int tune_mv = -1;  // launch-shape variant (rows, right-hand sides per block) of the fused finest up-leg + matvec, as well
   long long coarse_max = -1;  // points; -1: default (48^2 in 2D, 16^3 in 3D), 0: never
 
   // learned preconditioner (NULL: multigrid only)
@@ -1072,6 +1072,7 @@ int helm_setup(const helm_grid* grid, const float* n_map_dev, double k0, const h
 
   helm_ctx* c = new (std::nothrow) helm_ctx();
   if (!c) return fail(nullptr, HELM_ENOMEM, "out of host memory");
+  std::fill(c->tune_up, c->tune_up + HELM_MAX_LEVELS, -1);
   try {
     c->grid = *grid;
     c->abl = a;
@@ -1452,7 +1453,7 @@ int helm_autotune(helm_ctx* c, int B, const char* cache_path, helm_tune* out) {
   check(hipMemsetAsync(c->k.V, 0, (size_t)B * N0 * sizeof(c32), c->s), "memset");
   auto vcycle = [&] { mg_cycle(c, B, 0, r0, ScaleSet{nullptr, 0}, z0, true, nullptr); };
   if (!t.from_cache) {
-    for (int l = 0; l < HELM_MAX_LEVELS; ++l) c->tune_down[l] = c->tune_up[l] = 0;
+    for (int l = 0; l < HELM_MAX_LEVELS; ++l) c->tune_down[l] = 0, c->tune_up[l] = -1;
     c->coarse_max = -1;
     t.vcycle_default_ms = time_ms(c, vcycle, 3);
     // 1. fused-leg tiles, level by level, on the level's own buffers
@@ -1498,6 +1499,8 @@ int helm_autotune(helm_ctx* c, int B, const char* cache_path, helm_tune* out) {
           },
           5, 0.02);
     }
+    if (c->tune_mv == 0) c->tune_mv = mg_up_mv_default(c->lv[0].n, B);
+    for (int l = 0; l < HELM_MAX_LEVELS; ++l) c->tune_up[l] = std::max(c->tune_up[l], 0);
     // 3. the single-launch threshold for the coarse levels, on whole V-cycles
     if (c->o.coarse_single_launch) {
       const long long cand2[] = {0, 24LL * 24, 48LL * 48, 96LL * 96};

@@ -1248,6 +1248,16 @@ struct UpMvShape {
 };
 constexpr UpMvShape kUpMv[] = {{16, 4}, {12, 1}, {20, 1}, {28, 1}, {12, 2}, {12, 4}, {12, 6}, {20, 2}, {20, 4}};
 
+// Shapes of an untuned launch (cfg < 0): the first of each table, but where that makes fewer than
+// 1024 workgroups (four per CU) the launch lasts as long as one workgroup, so a smaller tile: 32 x
+// 16 points for the up-leg, 12 rows of one right-hand side for the up-leg with the matvec.  Solves
+// at 128^2, first shapes / smaller ones, ms: 1 right-hand side 10.2 / 9.7, 4 of them 12.2 / 9.9
+// (matvec shape alone), 16 13.7 / 11.5, 256^2 x 8 29.8 / 26.9, 400^2 x 4 47.5 / 42.7; gradient 256^2
+// x 32 95.7 / 91.5, FGMRES 203^2 x 7 31.3 / 29.8.  With 1480 and 2960 workgroups the matvec shape of
+// one right-hand side lost 1% (577^2 x 16 and x 30).  The down-legs' smaller tiles changed nothing.
+constexpr int SMALL_LAUNCH = 1024;
+int up_default(int n, int B) { return (long long)B * ((n + 63) / 64) * ((n + 15) / 16) < SMALL_LAUNCH ? 1 : 0; }
+
 template <int TCX, int TCY>
 void down_tile(hipStream_t s, int B, VecSet r, ScaleSet rs, LevelArgs lv, float omega, VecSet rc, int nc,
                const int* active, VecSet e) {
@@ -1324,6 +1334,7 @@ int mg_up_mv_rhs_per_block(int cfg) { return kUpMv[cfg].k; }
 
 void launch_up_mv2(hipStream_t s, int B, VecSet r, ScaleSet rs, LevelArgs lv, LevelArgs la, float omega, VecSet ec,
                    int nc, VecSet z, VecSet w, const int* active, int cfg) {
+  if (cfg < 0) cfg = mg_up_mv_default(lv.n, B);
 #define HELM_UP_MV(TY_, K_)                                                     \
   if (kUpMv[cfg].rows == TY_ && kUpMv[cfg].k == K_) {                           \
     up_mv2<TY_, K_>(s, B, r, rs, lv, la, omega, ec, nc, z, w, active);          \
@@ -1344,6 +1355,9 @@ void launch_step_fused2(hipStream_t s, int B, VecSet r, ScaleSet rs, LevelArgs l
 }
 
 int mg_down_variants() { return (int)(sizeof(kDown) / sizeof(kDown[0])); }
+int mg_up_mv_default(int n, int B) {
+  return (long long)((B + 3) / 4) * ((n + 59) / 60) * ((n + 15) / 16) < SMALL_LAUNCH ? 1 : 0;
+}
 int mg_up_variants() { return (int)(sizeof(kUp) / sizeof(kUp[0])); }
 void mg_down_shape(int cfg, int* tcx, int* tcy) {
   *tcx = kDown[cfg].tcx;
@@ -1386,6 +1400,7 @@ void launch_down_fused2(hipStream_t s, int B, VecSet r, ScaleSet rs, LevelArgs l
 
 void launch_up_fused2(hipStream_t s, int B, VecSet r, ScaleSet rs, LevelArgs lv, float omega, VecSet ec, int nc,
                       VecSet z, const int* active, int cfg, VecSet e) {
+  if (cfg < 0) cfg = up_default(lv.n, B);
   if (cfg == kUpCol) {
     constexpr int TX = 62, TY = 14;
     const int blocks = B * ((lv.n + TX - 1) / TX) * ((lv.n + TY - 1) / TY);

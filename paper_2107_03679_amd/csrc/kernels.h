@@ -48,7 +48,7 @@ inline int march_planes(long long columns, int n, int most, int least, int targe
 }
 
 // ---- multigrid legs (2D) ----
-// fused 2D legs; cfg selects one of the tile shapes (0 = default, see mg_*_shape).
+// fused 2D legs; cfg selects one of the tile shapes (see mg_*_shape; up-legs: < 0 by launch size).
 // e.p != NULL: repeated visit from the current solution e (right-hand side r - K e;
 // the up-leg writes e + correction to z, which must not alias e).
 void launch_down_fused2(hipStream_t s, int B, VecSet r, ScaleSet rs, LevelArgs lv, float omega, VecSet rc, int nc,
@@ -72,6 +72,7 @@ int mg_up_variants();
 // launch shapes of the fused finest up-leg + basis matvec (autotuner choices): tile
 // height and right-hand sides per block
 int mg_up_mv_variants();
+int mg_up_mv_default(int n, int B);  // the shape of an untuned launch on an n^2 grid
 int mg_up_mv_rows(int cfg);
 int mg_up_mv_rhs_per_block(int cfg);
 void mg_down_shape(int cfg, int* tcx, int* tcy);
