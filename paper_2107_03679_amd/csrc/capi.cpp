@@ -926,7 +926,8 @@ std::string tune_key(const helm_ctx* c, int B) {
   return buf;
 }
 
-// one cache entry per line: {"key": "...", "down": [..], "up": [..], "coarse_max": N}
+// one cache entry per line: {"key": "...", "down": [..], "up": [..], "coarse_max": N, "mv": V}; a line
+// without "mv" (or with one outside the table) means shape 0
 bool tune_load(helm_ctx* c, const char* path, const std::string& key) {
   FILE* f = std::fopen(path, "r");
   if (!f) return false;
@@ -959,7 +960,8 @@ bool tune_load(helm_ctx* c, const char* path, const std::string& key) {
     c->coarse_max = cm;
     int mv = 0;
     const char* pm = std::strstr(line, "\"mv\": ");
-    if (pm && std::sscanf(pm + 6, "%d", &mv) == 1 && mv >= 0 && mv < mg_up_mv_variants()) c->tune_mv = mv;
+    const bool valid = pm && std::sscanf(pm + 6, "%d", &mv) == 1 && mv >= 0 && mv < mg_up_mv_variants();
+    c->tune_mv = valid ? mv : 0;
     found = true;
   }
   std::fclose(f);
