@@ -18,6 +18,7 @@
 #include "kernels.h"
 #include "net_internal.h"
 #include "setup_host.h"
+#include "tune_pick.h"
 
 using helm_host::cd;
 
@@ -999,16 +1000,14 @@ double time_ms(helm_ctx* c, F&& f, int reps) {
 }
 
 // The fastest of nv launch variants: three interleaved rounds (clock ramps and drift
-// reach every variant alike), each variant's best mean over `reps` launches; ties go
-// to the lower index.  With a margin, variant 0 (the default) is kept unless another
-// is faster by more than that fraction.
+// reach every variant alike), each variant's best mean over `reps` launches, chosen by
+// pick_variant.
 template <class F>
-int fastest_variant(helm_ctx* c, int nv, F&& launch, int reps, double keep_default_within = 0.0) {
+int fastest_variant(helm_ctx* c, int nv, F&& launch, int reps, int base = 0, double margin = 0.0) {
   std::vector<double> best((size_t)nv, 1e30);
   for (int round = 0; round < 3; ++round)
     for (int v = 0; v < nv; ++v) best[v] = std::min(best[v], time_ms(c, [&] { launch(v); }, reps));
-  const int v = (int)(std::min_element(best.begin(), best.end()) - best.begin());
-  return best[v] < best[0] * (1.0 - keep_default_within) ? v : 0;
+  return pick_variant(best.data(), nv, base, margin);
 }
 
 }  // namespace
@@ -1485,10 +1484,10 @@ int helm_autotune(helm_ctx* c, int B, const char* cache_path, helm_tune* out) {
     }
     // 2. the launch shape of the fused finest up-leg + basis matvec (the s-step form's finest
     // step).  Timed alone (every right-hand side active, no graph) it ranks shapes within a
-    // few percent differently from inside the solve, where the default (16 rows, 4 right-hand
-    // sides per workgroup) measured fastest on MI355X at 512^2 x 60; the default is kept
-    // unless a variant is clearly faster.
-    c->tune_mv = 0;
+    // few percent differently from inside the solve, where the shape of an untuned launch (at
+    // 512^2 x 60: 16 rows, 4 right-hand sides per workgroup) measured fastest on MI355X; that
+    // shape is kept unless a variant is clearly faster.
+    c->tune_mv = mg_up_mv_default(c->lv[0].n, B);
     if (c->dim == 2 && c->o.fused && c->o.krylov == HELM_KRYLOV_SSTEP && c->o.fused_step == 2 && c->L >= 2) {
       const float om = (float)c->o.omega_jac;
       const Level& L1 = c->lv[1];
@@ -1499,9 +1498,8 @@ int helm_autotune(helm_ctx* c, int B, const char* cache_path, helm_tune* out) {
             launch_up_mv2(c->s, B, r0, ScaleSet{nullptr, 0}, level_K(c, 0), fine_A(c), om, VecSet{L1.e, L1.N}, L1.n,
                           z0, VecSet{c->d_T0, N0}, nullptr, v);
           },
-          5, 0.02);
+          5, c->tune_mv, 0.02);
     }
-    if (c->tune_mv == 0) c->tune_mv = mg_up_mv_default(c->lv[0].n, B);
     for (int l = 0; l < HELM_MAX_LEVELS; ++l) c->tune_up[l] = std::max(c->tune_up[l], 0);
     // 3. the single-launch threshold for the coarse levels, on whole V-cycles
     if (c->o.coarse_single_launch) {
