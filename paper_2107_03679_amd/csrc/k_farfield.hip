@@ -304,13 +304,14 @@ __global__ __launch_bounds__(256) void k_ff_adjoint(int dim, int B, int M, int n
 }
 
 // zeros outside Omega
-__global__ void k_ff_zero_layer(int dim, int ne, int w, int n, long long Ne, c32* s_ext, c32* rhs_ext) {
+__global__ void k_ff_zero_layer(int dim, int B, int ne, int w, int n, long long Ne, c32* s_ext, c32* rhs_ext) {
   const long long p = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (p >= Ne) return;
+  const int b = batch_index();
+  if (p >= Ne || b >= B) return;
   const Coord c = coord_of32((unsigned)p, (unsigned)ne, dim);
   const bool in = c.x >= w && c.x < w + n && c.y >= w && c.y < w + n && (dim == 2 || (c.z >= w && c.z < w + n));
   if (in) return;
-  const long long t = blockIdx.y * Ne + p;
+  const long long t = b * Ne + p;
   s_ext[t] = make_float2(0.f, 0.f);
   if (rhs_ext) rhs_ext[t] = make_float2(0.f, 0.f);
 }
@@ -379,7 +380,7 @@ void launch_ff_adjoint(hipStream_t s, int dim, int B, int M, int ne, int w, int 
                        const float* fpl, c32* s_ext, c32* rhs_ext) {
   const long long Ni = dim == 2 ? (long long)n * n : (long long)n * n * n;
   const long long Ne = dim == 2 ? (long long)ne * ne : (long long)ne * ne * ne;
-  hipLaunchKernelGGL(k_ff_zero_layer, dim3(nb(Ne, 256), B), dim3(256), 0, s, dim, ne, w, n, Ne, s_ext, rhs_ext);
+  hipLaunchKernelGGL(k_ff_zero_layer, batch_grid(nb(Ne, 256), B), dim3(256), 0, s, dim, B, ne, w, n, Ne, s_ext, rhs_ext);
   auto adjoint = [&](auto kernel, int bt) {
     hipLaunchKernelGGL(kernel, dim3(nb(Ni, FA_P), nb(B, 16 * bt)), dim3(256), 0, s, dim, B, M, ne, w, n, G, r, fpl, s_ext,
                        rhs_ext);
