@@ -60,11 +60,11 @@ __host__ __device__ __forceinline__ unsigned xcd_stretch(unsigned id, unsigned G
 // A launch of x workgroups for each of B right-hand sides.  A grid's second dimension ends at
 // 65536 (hipDeviceAttributeMaxGridDimY), a batch does not: the third takes over.  The kernel
 // returns where batch_index() is B or more.
+constexpr unsigned BATCH_Y = 32768;
 inline dim3 batch_grid(unsigned x, int B) {
-  const unsigned y = B < 32768 ? B : 32768;
-  return dim3(x, y, (B + y - 1) / y);
+  return dim3(x, (unsigned)B < BATCH_Y ? (unsigned)B : BATCH_Y, ((unsigned)B + BATCH_Y - 1) / BATCH_Y);
 }
-__device__ __forceinline__ int batch_index() { return (int)(blockIdx.z * gridDim.y + blockIdx.y); }
+__device__ __forceinline__ int batch_index() { return (int)(blockIdx.z * BATCH_Y + blockIdx.y); }
 
 // ---------------------------------------------------------------- complex64
 __host__ __device__ __forceinline__ c32 cadd(c32 a, c32 b) { return make_float2(a.x + b.x, a.y + b.y); }

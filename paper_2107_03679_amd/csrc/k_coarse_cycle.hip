@@ -311,11 +311,11 @@ constexpr int CD_MAXN = 640, CD_MP = 4;
 
 // MK: entries of a row per thread, ceil(Nc / CD_GRP) rounded up
 template <int DIM, int CD_ROWS, int MK>
-__global__ __launch_bounds__(CC_NT) void k_coarse_down_rows(CoarseCycleArgs a) {
+__global__ __launch_bounds__(CC_NT) void k_coarse_down_rows(int B, CoarseCycleArgs a) {
   constexpr int HALF = CD_ROWS / 32;  // columns per thread and pass: 1, or 2 with 64 rows
   extern __shared__ c32 lds[];
-  const int b = blockIdx.y;
-  if (a.active && !a.active[b]) return;
+  const int b = batch_index();
+  if (b >= B || (a.active && !a.active[b])) return;
   const float om = a.omega;
   const int tid = threadIdx.x, Nc = (int)a.lv[a.L - 1].N, row0 = blockIdx.x * CD_ROWS;
   const int rr = tid % CD_ROWS, row = row0 + rr;
@@ -472,12 +472,12 @@ bool coarse_cycle_split(const CoarseCycleArgs& a) {
 namespace {
 template <int DIM, int ROWS, int M0, int M1, int M2, int M3>
 void coarse_down_rows(hipStream_t s, int B, size_t lds, int Nc, const CoarseCycleArgs& a) {
-  const dim3 grid((Nc + ROWS - 1) / ROWS, B);
+  const dim3 grid = batch_grid((Nc + ROWS - 1) / ROWS, B);
   const int mk = (Nc * ROWS + CC_NT - 1) / CC_NT;
-  if (mk <= M0) hipLaunchKernelGGL((k_coarse_down_rows<DIM, ROWS, M0>), grid, dim3(CC_NT), lds, s, a);
-  else if (mk <= M1) hipLaunchKernelGGL((k_coarse_down_rows<DIM, ROWS, M1>), grid, dim3(CC_NT), lds, s, a);
-  else if (mk <= M2) hipLaunchKernelGGL((k_coarse_down_rows<DIM, ROWS, M2>), grid, dim3(CC_NT), lds, s, a);
-  else hipLaunchKernelGGL((k_coarse_down_rows<DIM, ROWS, M3>), grid, dim3(CC_NT), lds, s, a);
+  if (mk <= M0) hipLaunchKernelGGL((k_coarse_down_rows<DIM, ROWS, M0>), grid, dim3(CC_NT), lds, s, B, a);
+  else if (mk <= M1) hipLaunchKernelGGL((k_coarse_down_rows<DIM, ROWS, M1>), grid, dim3(CC_NT), lds, s, B, a);
+  else if (mk <= M2) hipLaunchKernelGGL((k_coarse_down_rows<DIM, ROWS, M2>), grid, dim3(CC_NT), lds, s, B, a);
+  else hipLaunchKernelGGL((k_coarse_down_rows<DIM, ROWS, M3>), grid, dim3(CC_NT), lds, s, B, a);
 }
 template <int DIM>
 void coarse_down(hipStream_t s, int B, size_t lds, int Nc, const CoarseCycleArgs& a) {

@@ -23,3 +23,15 @@ def test_sensor_adjoint():
         got = ctx.farfield_adjoint(r.repeat(REP, 1))
         for a, b in zip(got, want):
             assert bool((a.view(REP, *b.shape) == b).all())
+
+
+def test_coarse_levels_in_two_launches():
+    """A 12^2 coarsest grid (144 points) below 45^2 and 23^2."""
+    nmap = medium(29, seed=2)
+    with gpu_context(nmap, levels=3, max_batch=B, restart=1) as ctx:
+        assert ctx.info.coarsest_n == 12
+        r = to_dev(synth.complex_field((B, *ctx.grid_shape()), 21))
+        want = ctx.precondition(r)
+    with gpu_context(nmap, levels=3, max_batch=REP * B, restart=1) as ctx:
+        got = ctx.precondition(r.repeat(REP, 1, 1))
+    assert bool((got.view(REP, *want.shape) == want).all())
