@@ -76,7 +76,6 @@ struct helm_ctx {
   float h2_hi = 0, h2_lo = 0;
   std::vector<Level> lv;
   c32* d_minvT = nullptr;
-  double2* d_inv_work = nullptr;  // the coarsest operator being inverted (complex double)
   int* d_inv_flag = nullptr;      // set where it needs pivoting
   int Nc = 0;
 
@@ -95,8 +94,7 @@ struct helm_ctx {
   float* d_tv_mag = nullptr;   // [n^dim] TV magnitudes
   float* d_tv_part = nullptr;  // per-block TV partial sums
   double2* d_gram = nullptr;   // [maxB][nblk][(m+1)(m+2)/2] Gram partials of the s-step form
-  // inverse-problem workspace (allocated on first use): the FGP prox's buffers, index map
-  // from f
+  // inverse-problem workspace (set on first use): the FGP prox's buffers, index map from f
   FgpBufs inv{};
   float* d_inv_n = nullptr;
   double* d_inv_part = nullptr;
@@ -819,6 +817,20 @@ std::pair<float, float> split_ff(double v) {
   return {hi, (float)(v - (double)hi)};
 }
 
+// `bytes` of scratch for the length of a call in the Krylov basis, which holds nothing between calls
+// and is written before it is read in each; nullptr where it is smaller.
+void* basis_scratch(const helm_ctx* c, size_t bytes) {
+  return bytes <= (size_t)c->o.max_batch * (c->k.m + 1) * c->N0 * sizeof(c32) ? c->k.V : nullptr;
+}
+
+// Device memory of one call.
+struct TempBuffer {
+  void* p = nullptr;
+  ~TempBuffer() {
+    if (p) hipFree(p);
+  }
+};
+
 // Per medium: the Omega values of the fine planes and the coarse interiors on the GPU
 // (k_setup.hip), then the exact inverse of the coarsest shifted operator from that level's
 // coefficients (FP64, a few hundred to a few thousand unknowns; k_coarse_inverse.hip, on the host
@@ -853,7 +865,15 @@ void update_medium(helm_ctx* c, const float* n_map_dev) {
   check(hipGetLastError(), "set-up kernels");
   const Level& cl = c->lv[c->L - 1];
   check(hipMemcpyAsync(c->d_inv_flag, c->d_zero_ints, sizeof(int), hipMemcpyDeviceToDevice, c->s), "reset");
-  launch_coarse_inverse(c->s, c->dim, cl.n, cl.kc, cl.kclo, c->kbh * std::ldexp(1.0, c->L - 1), c->d_inv_work,
+  // the operator in complex double while it is inverted (268 MB at 4096 points: not kept)
+  const size_t work_bytes = coarse_inverse_work(c->Nc) * sizeof(double2);
+  TempBuffer own;
+  void* work = basis_scratch(c, work_bytes);
+  if (!work) {
+    check(hipMalloc(&own.p, work_bytes), "coarsest inverse");
+    work = own.p;
+  }
+  launch_coarse_inverse(c->s, c->dim, cl.n, cl.kc, cl.kclo, c->kbh * std::ldexp(1.0, c->L - 1), (double2*)work,
                         c->d_minvT, c->d_inv_flag);
   check(hipGetLastError(), "coarsest inverse");
   check(hipMemcpyAsync(c->h_status, c->d_inv_flag, sizeof(int), hipMemcpyDeviceToHost, c->s), "inverse flag");
@@ -1118,7 +1138,6 @@ int helm_setup(const helm_grid* grid, const float* n_map_dev, double k0, const h
     }
     c->Nc = (int)c->lv[c->L - 1].N;
     c->d_minvT = c->alloc<c32>((size_t)c->Nc * c->Nc);
-    c->d_inv_work = c->alloc<double2>(coarse_inverse_work(c->Nc));
     c->d_inv_flag = c->alloc<int>(1);
     c->d_nmap = c->alloc<float>(npts(c->n, c->dim));
     c->d_f = c->alloc<float>(N0);
@@ -1614,11 +1633,12 @@ namespace {
 void inv_reserve(helm_ctx* c) {
   if (!c->d_inv_n) c->d_inv_n = c->alloc<float>(npts(c->n, c->dim));
 }
-// the prox's buffers, one allocation
+// the prox's buffers, in the Krylov basis or one allocation
 void prox_reserve(helm_ctx* c) {
   if (c->inv.p[0]) return;
-  const size_t Ni = (size_t)npts(c->n, c->dim), Nd = c->dim * Ni;
-  float* m = c->alloc<float>(4 * Nd + 2 * Ni);
+  const size_t Ni = (size_t)npts(c->n, c->dim), Nd = c->dim * Ni, count = 4 * Nd + 2 * Ni;
+  float* m = (float*)basis_scratch(c, count * sizeof(float));
+  if (!m) m = c->alloc<float>(count);
   c->inv = FgpBufs{{m, m + Nd}, {m + 2 * Nd, m + 3 * Nd}, m + 4 * Nd, m + 4 * Nd + Ni};
 }
 }  // namespace
