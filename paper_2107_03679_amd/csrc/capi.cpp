@@ -103,7 +103,7 @@ struct helm_ctx {
   int ff_M = 0;
   c32* d_ffG = nullptr;
   c32* d_ff_src = nullptr;   // [maxB][n^dim] induced source
-  c32* d_ff_part = nullptr;  // partial sums of the sensor product
+  c32* d_ff_part = nullptr;  // [chunks][maxB][M]
   int ff_active_M = 0;       // sensors of the current set
   int* d_ff_iota = nullptr;  // 0 .. M-1 (the data residual of helm_farfield_residual)
   int* h_status = nullptr;  // pinned
@@ -1806,7 +1806,7 @@ int helm_farfield_set(helm_ctx* c, int M, const double* sensors_host) {
   const long long Ni = npts(c->n, dim);
   if (M > c->ff_M) {
     c->d_ffG = c->alloc<c32>((size_t)M * Ni + 1);  // one more: the adjoint reads pixels in pairs
-    c->d_ff_part = c->alloc<c32>(ff_part_size(Ni, c->o.max_batch, M));
+    c->d_ff_part = c->alloc<c32>(c->o.max_batch * ff_part_size(Ni, M));
     c->d_ff_iota = c->alloc<int>(M);
     std::vector<int> iota(M);
     for (int m = 0; m < M; ++m) iota[m] = m;

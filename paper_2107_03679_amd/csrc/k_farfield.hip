@@ -80,15 +80,13 @@ __global__ void k_ff_source(int dim, int B, int ne, int w, int n, const float* f
   s[(long long)b * Ni + i] = cscale(u, fpl[p]);
 }
 
-// part[k][b][m] = sum over pixels of G[m][i] s[b][i], k a piece of the grid or, with Q = 4, four
-// pieces in a row, each summed by itself.  The pieces follow from the pixel count alone
-// (ff_plan), so that a value has the same bits in any batch and any set of sensors, and no single
-// sum runs over more than a 256th of a large grid.  A wavefront takes 16 sensors and 16 BT
-// right-hand sides, so that G, the large operand, is read once for up to 64 right-hand sides: lane
-// group g loads pixels 8 g .. 8 g + 7 of every 32 (64 bytes a lane, 256 a row), the next 32 in
-// flight meanwhile.  Bound by the FP32 rate (16 n^d B M operations) and G's 8 M bytes per pixel.
-// 180 sensors, 32 right-hand sides, 256^2: 167 us with 32 x 32 LDS tiles on the vector units,
-// which read five LDS values for four products, 43 us now (the matrix cores' share 20).
+// part[k][b][m] = sum over pixel chunk k of G[m][i] s[b][i].  A wavefront takes 16 sensors and
+// 16 BT right-hand sides, so that G, the large operand, is read once for up to 64 right-hand
+// sides: lane group g loads pixels 8 g .. 8 g + 7 of every 32 (64 bytes a lane, 256 a row), the
+// next 32 in flight meanwhile.  Bound by the FP32 rate (16 n^d B M operations) and G's 8 M
+// bytes per pixel.  180 sensors, 32 right-hand sides, 256^2: 167 us with 32 x 32 LDS tiles on
+// the vector units, which read five LDS values for four products, 44 us now (the matrix cores'
+// share 20).
 struct Px8 {
   c32 v[8];
 };
@@ -112,61 +110,43 @@ __device__ __forceinline__ Px8 load_px8(const c32* row, long long i, long long i
   return o;
 }
 
-template <int BT, int Q>
-__global__ __launch_bounds__(256, BT == 4 ? 2 : 1) void k_ff_apply(int B, int M, long long Ni, long long piece, const c32* G,
+template <int BT>
+__global__ __launch_bounds__(256) void k_ff_apply(int B, int M, long long Ni, long long chunk, const c32* G,
                                                    const c32* s, c32* part) {
-  // sums over the pieces, each thread's own (in registers they would halve the occupancy)
-  __shared__ f32x4 sums[Q > 1 ? 2 * BT : 1][Q > 1 ? 256 : 1];
-  const int tid = threadIdx.x, lane = tid % 64, i16 = lane % 16, g = lane / 16;
-  const int m0 = (blockIdx.x * 4 + tid / 64) * 16, k = blockIdx.y, b0 = blockIdx.z * 16 * BT;
+  const int lane = threadIdx.x % 64, i16 = lane % 16, g = lane / 16;
+  const int m0 = (blockIdx.x * 4 + threadIdx.x / 64) * 16, k = blockIdx.y, b0 = blockIdx.z * 16 * BT;
   if (m0 >= M) return;
-  const long long i0 = k * Q * piece, i1 = min(i0 + Q * piece, Ni);
+  const long long i0 = (long long)k * chunk, i1 = min(i0 + chunk, Ni);
   // rows past the last sensor or right-hand side repeat it; their sums are not stored
   const c32* gr = G + (long long)min(m0 + i16, M - 1) * Ni;
   const c32* sr[BT];
 #pragma unroll
   for (int t = 0; t < BT; ++t) sr[t] = s + (long long)min(b0 + 16 * t + i16, B - 1) * Ni;
   f32x4 re[BT], im[BT];
+#pragma unroll
+  for (int t = 0; t < BT; ++t) re[t] = im[t] = f32x4{0.f, 0.f, 0.f, 0.f};
   Px8 gn = load_px8(gr, i0 + 8 * g, i1), sn[BT];
 #pragma unroll
   for (int t = 0; t < BT; ++t) sn[t] = load_px8(sr[t], i0 + 8 * g, i1);
-  for (long long p0 = i0; p0 < i1; p0 += Q > 1 ? piece : i1 - i0) {
-    const long long p1 = Q > 1 ? min(p0 + piece, i1) : i1;
+  for (long long ib = i0; ib < i1; ib += 32) {
+    const Px8 gv = gn;
+    Px8 sv[BT];
 #pragma unroll
-    for (int t = 0; t < BT; ++t) re[t] = im[t] = f32x4{0.f, 0.f, 0.f, 0.f};
-    for (long long ib = p0; ib < p1; ib += 32) {
-      const Px8 gv = gn;
-      Px8 sv[BT];
+    for (int t = 0; t < BT; ++t) sv[t] = sn[t];
+    if (ib + 32 < i1) {
+      gn = load_px8(gr, ib + 32 + 8 * g, i1);
 #pragma unroll
-      for (int t = 0; t < BT; ++t) sv[t] = sn[t];
-      if (ib + 32 < i1) {
-        gn = load_px8(gr, ib + 32 + 8 * g, i1);
-#pragma unroll
-        for (int t = 0; t < BT; ++t) sn[t] = load_px8(sr[t], ib + 32 + 8 * g, i1);
-      }
-#pragma unroll
-      for (int v = 0; v < 8; ++v)
-#pragma unroll
-        for (int t = 0; t < BT; ++t) {
-          re[t] = mfma4(gv.v[v].x, sv[t].v[v].x, re[t]);
-          im[t] = mfma4(gv.v[v].x, sv[t].v[v].y, im[t]);
-          re[t] = mfma4(-gv.v[v].y, sv[t].v[v].y, re[t]);
-          im[t] = mfma4(gv.v[v].y, sv[t].v[v].x, im[t]);
-        }
+      for (int t = 0; t < BT; ++t) sn[t] = load_px8(sr[t], ib + 32 + 8 * g, i1);
     }
-    if constexpr (Q > 1) {  // the pieces in order, as k_ff_reduce adds them
+#pragma unroll
+    for (int v = 0; v < 8; ++v)
 #pragma unroll
       for (int t = 0; t < BT; ++t) {
-        if (p0 != i0) {
-          re[t] = sums[2 * t][tid] + re[t];
-          im[t] = sums[2 * t + 1][tid] + im[t];
-        }
-        if (p1 < i1) {
-          sums[2 * t][tid] = re[t];
-          sums[2 * t + 1][tid] = im[t];
-        }
+        re[t] = mfma4(gv.v[v].x, sv[t].v[v].x, re[t]);
+        im[t] = mfma4(gv.v[v].x, sv[t].v[v].y, im[t]);
+        re[t] = mfma4(-gv.v[v].y, sv[t].v[v].y, re[t]);
+        im[t] = mfma4(gv.v[v].y, sv[t].v[v].x, im[t]);
       }
-    }
   }
 #pragma unroll
   for (int t = 0; t < BT; ++t) {
@@ -179,32 +159,22 @@ __global__ __launch_bounds__(256, BT == 4 ? 2 : 1) void k_ff_apply(int B, int M,
   }
 }
 
-// y[b][m] = sum over the partial sums, PER of them (four pieces, or their sum) at a time, in one
-// fixed order: four threads take every fourth group, sixteen (eight) loads in flight, past the
-// last partial sum of its value and as zeros
-template <int PER>
-__global__ __launch_bounds__(256) void k_ff_reduce(int count, int npart, const c32* part, c32* y) {
-  constexpr int U = PER == 4 ? 4 : 8;
+// y[b][m] = sum over chunks (fixed order: four threads take every fourth chunk, eight loads in
+// flight)
+__global__ __launch_bounds__(256) void k_ff_reduce(int count, int nsplit, const c32* part, c32* y) {
   __shared__ c32 red[4][64];
   const int e = threadIdx.x % 64, q = threadIdx.x / 64, t = blockIdx.x * 64 + e;
-  const c32* p = part + min(t, count - 1);
   c32 a = make_float2(0.f, 0.f);
-  for (int j = q; j * PER < npart; j += 4 * U) {
-    c32 v[U][PER];
+  if (t < count) {
+    int k = q;
+    for (; k + 28 < nsplit; k += 32) {
+      c32 v[8];
 #pragma unroll
-    for (int u = 0; u < U; ++u)
+      for (int u = 0; u < 8; ++u) v[u] = part[(long long)(k + 4 * u) * count + t];
 #pragma unroll
-      for (int o = 0; o < PER; ++o) v[u][o] = p[(long long)min((j + 4 * u) * PER + o, npart - 1) * count];
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-#pragma unroll
-      for (int o = 0; o < PER; ++o) {
-        const bool in = (j + 4 * u) * PER + o < npart;
-        v[u][o] = make_float2(in ? v[u][o].x : 0.f, in ? v[u][o].y : 0.f);
-        if (o) v[u][0] = cadd(v[u][0], v[u][o]);
-      }
-      a = cadd(a, v[u][0]);
+      for (int u = 0; u < 8; ++u) a = cadd(a, v[u]);
     }
+    for (; k < nsplit; k += 4) a = cadd(a, part[(long long)k * count + t]);
   }
   red[q][e] = a;
   __syncthreads();
@@ -327,53 +297,41 @@ void launch_ff_matrix(hipStream_t s, int dim, int n, int M, const double* sens, 
                      G);
 }
 
-namespace {
-// The pieces of the grid whose sums are formed one by one: at least 256 pixels, at most 256
-// pieces, whole steps of 32.
-struct FfPlan {
-  long long piece;
-  int pieces;
+// Pixel chunks of the sensor product: between `least`, 64 of at least 1024 pixels (no FP32 sum runs
+// over more than a 64th of a large grid), and `most`, 256 of at least 256.
+struct FfChunks {
+  long long least, most;
 };
-FfPlan ff_plan(long long Ni) {
-  const long long k = std::min(std::max(Ni / 256, 1LL), 256LL);
-  FfPlan p;
-  p.piece = ((Ni + k - 1) / k + 31) / 32 * 32;
-  p.pieces = (int)((Ni + p.piece - 1) / p.piece);
-  return p;
+static FfChunks ff_chunks(long long Ni) {
+  return {std::min(std::max(Ni / 1024, 1LL), 64LL), std::min(std::max(Ni / 256, 1LL), 256LL)};
 }
-constexpr int FF_WAVES = 2048;  // two wavefronts per SIMD
-}  // namespace
+constexpr long long FF_WAVES = 2048;  // two wavefronts per SIMD
 
-// Partial sums launch_ff_forward writes at most: of four pieces each, or of single ones where a
-// launch by fours has fewer than FF_WAVES wavefronts of at least one sensor and right-hand side,
-// at most 16 x 64 of them, each
-size_t ff_part_size(long long Ni, int B, int M) {
-  const FfPlan p = ff_plan(Ni);
-  const long long quads = (p.pieces + 3) / 4, bm = (long long)B * M;
-  return (size_t)std::max(quads * bm, p.pieces * std::min(bm, 16LL * 64 * FF_WAVES / quads));
+// Partial sums per right-hand side for any number of sensors up to M (the chunks that
+// launch_ff_forward wants times the sensors are at most FF_WAVES 16)
+size_t ff_part_size(long long Ni, int M) {
+  const FfChunks c = ff_chunks(Ni);
+  return (size_t)std::max(c.least * M, std::min(c.most * M, FF_WAVES * 16));
 }
 
 void launch_ff_forward(hipStream_t s, int dim, int B, int M, int ne, int w, int n, const float* fpl, const c32* uin,
                        const c32* usc, const c32* G, c32* src, c32* part, c32* y) {
   const long long Ni = dim == 2 ? (long long)n * n : (long long)n * n * n;
   hipLaunchKernelGGL(k_ff_source, dim3(nb(Ni, 256), B), dim3(256), 0, s, dim, B, ne, w, n, fpl, uin, usc, src);
-  const FfPlan p = ff_plan(Ni);
-  const int bt = B <= 16 ? 1 : (B <= 32 ? 2 : 4), quads = (p.pieces + 3) / 4;
-  // Four pieces per wavefront where that fills the chip (a quarter of the partial sums).  Against
-  // chunks sized for 2048 wavefronts, whose sums depend on the batch: residual and adjoint with
-  // 360 sensors at 48^3 x 60 790 -> 726 us, 256^2 x 60 361 -> 359, 200^2 x 1 109 -> 111; 180
-  // sensors at 256^2 x 32 150 -> 148, 90 at 101^2 x 17 81 -> 81.
-  const bool by4 = (long long)nb(M, 16) * nb(B, 16 * bt) * quads >= FF_WAVES;
-  const int npart = by4 ? quads : p.pieces;
-  auto apply = [&](auto kernel) {
-    hipLaunchKernelGGL(kernel, dim3(nb(M, 64), npart, nb(B, 16 * bt)), dim3(256), 0, s, B, M, Ni, p.piece, G, src, part);
+  // Chunks for FF_WAVES wavefronts over the sensor tiles (up to 64 right-hand sides are one tile of
+  // them).  From the pixels and the sensors alone: with the right-hand sides counted too, a source
+  // had other last bits in a batch of 65.
+  const FfChunks c = ff_chunks(Ni);
+  const long long ns = std::max(c.least, std::min(c.most, FF_WAVES / nb(M, 16)));
+  const long long chunk = ((Ni + ns - 1) / ns + 31) / 32 * 32;
+  const int used = (int)((Ni + chunk - 1) / chunk);
+  auto apply = [&](auto kernel, int bt) {
+    hipLaunchKernelGGL(kernel, dim3(nb(M, 64), used, nb(B, 16 * bt)), dim3(256), 0, s, B, M, Ni, chunk, G, src, part);
   };
-  if (bt == 1) by4 ? apply(k_ff_apply<1, 4>) : apply(k_ff_apply<1, 1>);
-  else if (bt == 2) by4 ? apply(k_ff_apply<2, 4>) : apply(k_ff_apply<2, 1>);
-  else by4 ? apply(k_ff_apply<4, 4>) : apply(k_ff_apply<4, 1>);
-  const dim3 grid(nb((long long)B * M, 64));
-  if (by4) hipLaunchKernelGGL(k_ff_reduce<1>, grid, dim3(256), 0, s, B * M, npart, part, y);
-  else hipLaunchKernelGGL(k_ff_reduce<4>, grid, dim3(256), 0, s, B * M, npart, part, y);
+  if (B <= 16) apply(k_ff_apply<1>, 1);
+  else if (B <= 32) apply(k_ff_apply<2>, 2);
+  else apply(k_ff_apply<4>, 4);
+  hipLaunchKernelGGL(k_ff_reduce, dim3(nb((long long)B * M, 64)), dim3(256), 0, s, B * M, used, part, y);
 }
 
 void launch_ff_adjoint(hipStream_t s, int dim, int B, int M, int ne, int w, int n, const c32* G, const c32* r,

@@ -285,7 +285,7 @@ void launch_index_from_f(hipStream_t s, long long count, const float* f, double 
 // ---- sensor operator (far field through the Lippmann-Schwinger integral) ----
 void launch_ff_matrix(hipStream_t s, int dim, int n, int M, const double* sens, double kbh, double h,
                       const double2* tab, double x0, double dx, int ntab, c32* G);
-size_t ff_part_size(long long Ni, int B, int M);
+size_t ff_part_size(long long Ni, int M);
 void launch_ff_forward(hipStream_t s, int dim, int B, int M, int ne, int w, int n, const float* fpl, const c32* uin,
                        const c32* usc, const c32* G, c32* src, c32* part, c32* y);
 void launch_ff_adjoint(hipStream_t s, int dim, int B, int M, int ne, int w, int n, const c32* G, const c32* r,
