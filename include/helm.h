@@ -105,7 +105,8 @@ typedef struct {
   int fused;        /* 1 = fused multigrid leg kernels (2D and 3D) when nu1 = nu2 = 1 (1) */
   int use_graph;    /* 1 = replay each restart cycle as a captured hipGraph (1) */
   int coarse_single_launch; /* 1 = V-cycle levels with <= 48^2 (2D) / 16^3 (3D) points run
-                               in one launch, one workgroup per right-hand side (1) */
+                               in one launch, one workgroup per right-hand side, or in two
+                               where the coarsest grid has 129 to 640 points (1) */
   int krylov;       /* HELM_KRYLOV_SSTEP (default), HELM_KRYLOV_FGMRES or HELM_KRYLOV_BICGSTAB */
   int fused_step;   /* finest level of the s-step form (2D, fused legs): 0 = separate kernels;
                        1 = the work between two coarse visits (up-leg, basis matvec, next
@@ -169,7 +170,8 @@ int helm_extended_size(int n, int abl_width, int levels);
 
 /* Create a context: coefficient c = (k0 h)^2 eta^2 alpha on Omega_e and its
  * restrictions per level (Sec. IV-C: full weighting, background ring), the
- * exact inverse of the coarsest K_kappa (factorised on the host in FP64),
+ * exact inverse of the coarsest K_kappa (FP64, on the GPU; on the host with
+ * pivoting where a row is not diagonally dominant),
  * the Krylov workspace for opts->max_batch right-hand sides.
  *   n_map_dev : device float[n^dim], the refractive index on Omega (copied)
  *   k0        : free-space wavenumber omega/c in the unit of 1/h
@@ -486,7 +488,7 @@ typedef struct {
   int down[HELM_TUNE_MAX_LEVELS][2];    /* fused down-leg tile per level: coarse TCX x TCY points */
   int up[HELM_TUNE_MAX_LEVELS][3];      /* fused up-leg tile per level: fine TX x TY, PY points per thread
                                            (PY 0: one column per lane, every fourth row) */
-  long long coarse_max;                 /* levels with at most this many points run in one launch */
+  long long coarse_max;                 /* levels with at most this many points run in one launch (or two) */
   double vcycle_ms;                     /* one preconditioner cycle for B right-hand sides, chosen shapes */
   double vcycle_default_ms;             /* ... with the default shapes (0 when from_cache) */
   int up_mv_rows;                       /* tile height of the fused finest up-leg + basis matvec (s-step form) */
@@ -497,7 +499,7 @@ typedef struct {
  * the method's many-right-hand-side solves): times every tile shape of the
  * fused 2D down- and up-legs on each level with B right-hand sides, the tile
  * height of the s-step form's fused finest up-leg + basis matvec, then the
- * threshold below which the coarse levels run as one launch, and keeps the
+ * threshold below which the coarse levels run as one launch or two, and keeps the
  * fastest for the following solves of this context (results do not depend on
  * the shapes: every point is computed by the same arithmetic).  cache_path
  * (nullable) is a JSON-lines file keyed by GPU architecture, dimension, grid,

@@ -332,7 +332,7 @@ void mg_cycle(helm_ctx* c, int B, int l, VecSet r, ScaleSet rs, VecSet out, bool
   const long long small = coarse_small(c);
   if (vcycle11 && l >= 1 && c->o.coarse_single_launch && fine.N <= small && rs.p == nullptr && r.stride == fine.N &&
       out.stride == fine.N && eres.p == nullptr && !accumulate) {
-    // levels l .. L-1 in one launch, one workgroup per right-hand side
+    // levels l .. L-1 in one launch, one workgroup per right-hand side, or in two
     CoarseCycleArgs a{};
     a.dim = dim;
     a.lp = l;

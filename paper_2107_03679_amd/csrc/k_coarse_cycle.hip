@@ -1,8 +1,9 @@
 // The coarse part of a V-cycle (Alg. 2, nu1 = nu2 = 1, zero initial guess)
-// for levels lp .. L-1 in ONE launch: one workgroup per right-hand side.
+// for levels lp .. L-1 in one launch, one workgroup per right-hand side, or in
+// two where the coarsest product is the long part (second half of this file).
 // The right-hand sides are independent, so every sweep of a level only
 // needs a workgroup barrier; the level buffers of one right-hand side stay
-// in L2.  Per level l (h_l^2-scaled operators, W = omega / diag(K_l)):
+// in LDS or L2.  Per level l (h_l^2-scaled operators, W = omega / diag(K_l)):
 //   down: e = W r;  t = r - K e = (1 - w) r + sum of neighbours of e;  r_{l+1} = 4 R t
 //   coarsest: e = K^-1 r (explicit inverse)
 //   up:   t = e + P e_{l+1};  e = (1 - w) t + W (r + sum of neighbours of t)
@@ -309,7 +310,7 @@ __global__ __launch_bounds__(CC_NT) void k_coarse_cycle_lds(CoarseCycleArgs a) {
 // the single launch's LDS) 91.8 -> 64.6.
 constexpr int CD_MAXN = 640, CD_MP = 4;
 
-// MK: entries of a row per thread, ceil(Nc / CD_GRP) rounded up
+// MK: entries of a row per thread, ceil(Nc CD_ROWS / CC_NT) or more
 template <int DIM, int CD_ROWS, int MK>
 __global__ __launch_bounds__(CC_NT) void k_coarse_down_rows(int B, CoarseCycleArgs a) {
   constexpr int HALF = CD_ROWS / 32;  // columns per thread and pass: 1, or 2 with 64 rows

@@ -9,12 +9,11 @@ namespace {
 
 constexpr int PW_DIRS = 256;
 
-// rhs_q(p) = f(p) * prod_axis T_q,axis(coord_axis(p)): the plane wave
-// exp(j k_b <d_q, x - x_c>) factorises over axes; the per-axis factors are
-// tabulated in FP64 and rounded once to complex64.  (On the host the tables of
-// 60 plane waves at 577^2 were 0.6 ms of sines and cosines and an upload.)
-// Phase tables exp(j k_b h d_a (i - centre)) of up to PW_DIRS direction components (b, a):
-// tables[(b dim + a) n + i].  The phase and its sine and cosine in FP64, rounded once.
+// The plane wave exp(j k_b <d_q, x - x_c>) factorises over axes.  Phase tables
+// T_b,a(i) = exp(j k_b h d_a (i - centre)) of up to PW_DIRS direction components (b, a), at
+// tables[(b dim + a) n + i]: the phase and its sine and cosine in FP64, rounded once to
+// complex64.  (On the host the tables of 60 plane waves at 577^2 were 0.6 ms of sines and
+// cosines and an upload.)
 struct PlaneDirs {
   double d[PW_DIRS];
 };
@@ -27,8 +26,8 @@ __global__ void k_plane_tables(int count, int n, double kbh, double centre, Plan
   tables[t] = make_float2((float)cs, (float)sn);
 }
 
-// u_in = product of the axes' phases, rhs = f u_in; a point's coordinates and f serve PW_B
-// right-hand sides.
+// u_in,q(p) = prod_axis T_q,axis(coord_axis(p)), rhs_q = f u_in,q; a point's coordinates and f
+// serve PW_B right-hand sides.
 constexpr int PW_B = 4;
 __global__ void k_plane_wave(int dim, int B, int n, long long N, const float* fplane, const c32* tables, c32* rhs,
                              c32* uin) {

@@ -1161,10 +1161,10 @@ __global__ void k_apply(int dim, VecSet x, ScaleSet xs, LevelArgs lv, float out_
 }
 
 // Z = M R, the exact coarsest solve of a batch, with M given transposed (minvT[k Nc + row] =
-// M[row][k]) and read once per BT right-hand sides.  A workgroup takes 16 rows: threads (row, column group), 64 groups, each with the entries of its columns
-// loaded straight from memory (128 bytes a column, KC columns ahead of the products) and R
-// passing through LDS, KC columns at a time; then the groups' sums are added in a fixed order.
-// No partial sums leave the workgroup.  Bound by the inverse's 8 Nc^2 bytes: 24 MB at 12^3, in
+// M[row][k]) and read once per BT right-hand sides.  A workgroup takes 16 rows: threads (row,
+// column group), 64 groups, each with the entries of its columns loaded straight from memory (128
+// bytes a column, KC columns ahead of the products) and R passing through LDS, KC columns at a
+// time; then the groups' sums are added in a fixed order.  No partial sums leave the workgroup.  Bound by the inverse's 8 Nc^2 bytes: 24 MB at 12^3, in
 // 21 us for 8 right-hand sides (45 + 5 with 64-row tiles, eight column slices and a second
 // launch; the same product with one thread per row, for fewer than four right-hand sides, made a
 // cycle at 100^3 x 1 208 us, now 126).

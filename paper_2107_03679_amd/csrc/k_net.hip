@@ -1288,9 +1288,10 @@ __global__ __launch_bounds__(256) void k_res_ratio(int D, int H, int W, const fl
   }
 }
 
-// Adam on the FP32 master weights (entries with mask 0 -- the padding -- stay 0)
-// One launch each for all layers: with one per tensor and layer (24, each for at most some ten
-// thousand entries) a training step on 4 crops of 256^2 took 976 us instead of 856.
+// Adam on the FP32 master weights (entries with mask 0 -- the padding -- stay 0), and below the
+// packing of the new weights: one launch each for all layers.  With one per tensor and layer (24,
+// each for at most some ten thousand entries) a training step on 4 crops of 256^2 took 976 us
+// instead of 856.
 __global__ void k_adam(AdamArgs a) {
   int l = 0;
   while (l + 1 < a.n && (int)blockIdx.x >= a.T[l + 1].block0) ++l;
@@ -1308,6 +1309,10 @@ __global__ void k_adam(AdamArgs a) {
   T.v[t] = vt;
   T.w[t] -= a.lr * (mt * a.c1) / (sqrtf(vt * a.c2) + a.eps);
 }
+
+// Pack FP32 master weights W[co][k] (k = tap * cin + ci) into the BF16 forward layout and the
+// BF16 backward-data layout Wb[ci][tap' * cob + co] = W[co][(ntaps - 1 - tap') * cin + ci]
+// (wb_rows >= cin rows; rows past cin, read by the last output tile, are zero).
 __global__ void k_pack(PackArgs a) {
   int l = 0;
   while (l + 1 < a.n && (int)blockIdx.x >= a.L[l + 1].block0) ++l;

@@ -14,7 +14,7 @@
 // layer in a fixed order.
 // (Fetching both operands element by element for every (16 k-values, 16 channels) tile, the
 // weight gradients were 1.35 of the 2.42 ms of a training step on 4 images of 256^2, the
-// biases' sums and the 16 reductions 0.25 ms; they are 0.13 and 0.02 ms of 1.03 now.  The
+// biases' sums and the 16 reductions 0.25 ms; they are 0.13 and 0.02 ms of 0.89 now.  The
 // blocks wait for their tiles' loads: the matrix cores would take 0.02 ms.)
 #include <algorithm>
 

@@ -37,10 +37,10 @@ enum {
 // Planes one workgroup of a 3D marching kernel walks: `most` halved (down to `least`) until
 // the launch has `target` workgroups, by default 1024, four per CU.  A march is a serial chain of
 // about a microsecond a plane, and small levels or batches would leave most CUs idle behind a few
-// long ones: with 16 (down-leg: 8 coarse) planes throughout, the legs of a 29^3 x 8 level took
-// 22-38 us of a cycle, and the 64^3 x 8 solve 64.6 ms instead of 50.6.  Targets of 256 / 512 /
-// 1024 / 2048 / 4096 workgroups gave 56.8 / 51.5 / 50.6 / 50.2 / 52.8 ms, a cycle at 128^3 x 8
-// 780 / 769 / 771 / 776 / 794 us.  Every point is computed by the same arithmetic whatever the march.
+// long ones.  Targets of 256 / 512 / 1024 / 2048 / 4096 workgroups: 64^3 x 8 solve 44.7 / 43.9 /
+// 43.5 / 44.3 / 45.3 ms, a cycle at 128^3 x 8 601 / 600 / 605 / 619 / 659 us, at 90^3 x 2 138 / 135 /
+// 145 / 148 / 157, at 32^3 x 2 66 / 62 / 65 / 65 / 65.  Every point is computed by the same arithmetic
+// whatever the march.
 inline int march_planes(long long columns, int n, int most, int least, int target = 1024) {
   int p = most;
   while (p > least && columns * ((n + p - 1) / p) < target) p = (p + 1) / 2;
@@ -95,7 +95,7 @@ void launch_level_residual(hipStream_t s, int dim, int B, VecSet bvec, VecSet v,
                            const int* active, ScaleSet bs = ScaleSet{nullptr, 0});
 void launch_add(hipStream_t s, int B, VecSet x, VecSet y, long long N, const int* active);
 
-// ---- coarse levels of a V-cycle in one launch (one workgroup per right-hand side) ----
+// ---- coarse levels of a V-cycle in one launch (one workgroup per right-hand side) or two ----
 struct CoarseLevel {
   int n;
   long long N;
@@ -255,7 +255,7 @@ void launch_setup_fine(hipStream_t s, const SetupFineArgs& a);
 void launch_setup_coarse(hipStream_t s, int dim, int nf, int nc, const c32* kcf, const c32* kcflo, float omega,
                          c32* kcc, c32* kcclo, c32* wdc);
 
-// Inverse of the coarsest K'_l (complex double, dense, padded to coarse_inverse_rows(Nc) rows)
+// Inverse of the coarsest K'_l (complex double, dense, padded to whole blocks of 32 rows)
 // without pivoting, written as float to minvT; kc, kclo: kappa c of the level as float-float,
 // ghost_im: k_b h_l.  work: coarse_inverse_work(Nc) entries.  *flag (device): 0 where every
 // row is finite and diagonally dominant, else 1 and minvT is not to be used.

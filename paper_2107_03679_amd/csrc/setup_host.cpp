@@ -6,9 +6,9 @@
 //    h_l^2-scaled operators), background value k_b^2 h_l^2 alpha(x) on the
 //    outermost ring;
 //  * the explicit inverse of the coarsest shifted operator, which the GPU applies
-//    as a dense product: banded LU without pivoting where the operator is
-//    diagonally dominant (the usual case: the shifted coefficient of the
-//    coarsest grid is large), else Gauss-Jordan with partial pivoting.
+//    as a dense product, by Gauss-Jordan with partial pivoting: for operators
+//    with a row that is not diagonally dominant (the GPU inverts the others,
+//    the usual case: the shifted coefficient of the coarsest grid is large).
 #include "setup_host.h"
 
 #include <algorithm>
