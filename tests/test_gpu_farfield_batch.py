@@ -19,7 +19,7 @@ def _sensors(n, dim, M):
     return v / np.linalg.norm(v, axis=1, keepdims=True) * (n * np.sqrt(dim) / 2 + 3)
 
 
-# 125^2: 27 chunks of 608 pixels, the last one partly filled; 256^2: 170 asked for
+# 125^2: 26 chunks of 608 pixels, the last one partly filled; 256^2: 158 of 416
 @pytest.mark.parametrize("dim, n, M", [(2, 125, 1200), (2, 256, 180), (3, 19, 70)])
 def test_values_do_not_depend_on_the_batch(dim, n, M):
     nmap = medium(n, d=dim, seed=6)
@@ -43,3 +43,18 @@ def test_values_do_not_depend_on_the_batch(dim, n, M):
     # single-precision G and sums: some 1200 roundings of a chunk's partial sums, which are a few
     # tenths of the value, in quadrature
     assert rel(to_np(y)[:, few], ref) < 2e-6
+
+
+def test_many_sensors_keep_their_sums_short():
+    """4096 sensors at 256^2: wavefronts enough with 8 chunks, but 64 of 1024 pixels are taken."""
+    nmap = medium(256, seed=6)
+    prob = oracle_problem(nmap, w=4, levels=4)
+    sens = _sensors(256, 2, 4096)
+    u = synth.complex_field((2, *prob.shape), 92).astype(np.complex64)
+    with gpu_context(nmap, w=4, levels=4, max_batch=2, restart=1) as ctx:
+        ctx.farfield_set(sens)
+        y = to_np(ctx.farfield(to_dev(u)))
+    few = slice(0, 4096, 200)
+    inner = (slice(None),) + prob.interior_slices()
+    ref = (scattering_potential(prob) * u)[inner].reshape(2, -1) @ sensor_matrix(prob, sens[few]).T
+    assert rel(y[:, few], ref) < 2e-6  # some 2000 roundings of a chunk's partial sums, as above
